@@ -373,6 +373,40 @@ int hg_refine_graph_create(const float *img, const float *tgt, int32_t B, int32_
                            int32_t iters, float step, float *offsets, float *loss, void *stream,
                            hg_graph **out);
 
+/* The same calls with a workspace. A batch of few patches leaves most compute
+ * units idle when each patch has one workgroup; with a workspace its patches
+ * are cut into parts over several workgroups (double sums per part in ws, added
+ * in a fixed order by a second, small launch; a refinement step adds them in
+ * the next step's prologue). Results differ from the calls without a workspace
+ * only by the order of those sums.
+ *   ws: at least hg_photometric_ws_bytes(B, h, w) resp. hg_refine_ws_bytes
+ *   bytes (0: a batch of this shape is not cut), 16-byte aligned, not shared
+ *   with a call that may overlap; contents before and after do not matter.
+ *   NULL: as the calls above. A graph keeps its ws until it is destroyed.
+ * Too small a ws -> HG_EWORKSPACE; other errors as above.                    */
+size_t hg_photometric_ws_bytes(int32_t B, int32_t h, int32_t w);
+size_t hg_refine_ws_bytes(int32_t B, int32_t h, int32_t w);
+int hg_warp_l1_fwd_ws(const double *H, const float *img, const float *tgt, int32_t B, int32_t h,
+                      int32_t w, float *loss, void *ws, size_t ws_bytes, void *stream);
+int hg_warp_l1_bwd_ws(const double *H, const float *img, const float *tgt, const float *grad_loss,
+                      int32_t B, int32_t h, int32_t w, double *grad_H, void *ws, size_t ws_bytes,
+                      void *stream);
+int hg_photometric_fwd_ws(const float *offsets, const float *img, const float *tgt, int32_t B,
+                          int32_t h, int32_t w, float *loss, void *ws, size_t ws_bytes,
+                          void *stream);
+int hg_photometric_bwd_ws(const float *offsets, const float *img, const float *tgt,
+                          const float *grad_loss, int32_t B, int32_t h, int32_t w,
+                          float *grad_offsets, void *ws, size_t ws_bytes, void *stream);
+int hg_photometric_fwd_grad_ws(const float *offsets, const float *img, const float *tgt,
+                               int32_t B, int32_t h, int32_t w, float *loss, float *grad_unit,
+                               void *ws, size_t ws_bytes, void *stream);
+int hg_refine_ws(const float *img, const float *tgt, int32_t B, int32_t h, int32_t w,
+                 int32_t iters, float step, float *offsets, float *loss, void *ws,
+                 size_t ws_bytes, void *stream);
+int hg_refine_graph_create_ws(const float *img, const float *tgt, int32_t B, int32_t h, int32_t w,
+                              int32_t iters, float step, float *offsets, float *loss, void *ws,
+                              size_t ws_bytes, void *stream, hg_graph **out);
+
 /* Plain stored-intermediate form of the same pipeline (for comparison):
  * warp -> warped (B x h x w floats) ; L1 -> loss ; its backward ->
  * grad_warped (floats) ; warp backward from grad_warped -> grad_H (doubles).

@@ -8,6 +8,7 @@ in the library's HIP kernels. Function names match the C entry points.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 
 import torch
 
@@ -381,7 +382,10 @@ class Graph:
         self.owner = owner
 
     def launch(self, stream=None):
-        _abi.call("hg_graph_launch", self.h, _stream(stream))
+        raw = _stream(stream)
+        if isinstance(self.owner, Refine):
+            self.owner._record(raw, stream)
+        _abi.call("hg_graph_launch", self.h, raw)
 
     def close(self):
         if self.h:
@@ -493,13 +497,33 @@ def _img3(img, name):
     return img.shape
 
 
+@functools.lru_cache(maxsize=1024)
+def _part_ws_bytes(B, h, w):
+    return _abi.lib().hg_photometric_ws_bytes(B, h, w)
+
+
+def _part_ws(B, h, w, device, stream):
+    """(pointer, bytes) of a workspace for a batch whose patches are cut into
+    parts, and the tensor that holds it; (None, 0) and None when the batch is
+    not cut. The allocator hands the memory out again in stream order, so a
+    call on another stream than the current one is recorded."""
+    n = _part_ws_bytes(B, h, w)
+    if not n:
+        return (None, 0), None
+    ws = torch.empty(n, dtype=torch.uint8, device=device)
+    if stream is not None:
+        ws.record_stream(stream)
+    return (ws.data_ptr(), n), ws
+
+
 def hg_warp_l1_fwd(H, img, tgt, stream=None):
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
     _c(H, "H", torch.float64)
     loss = torch.empty(B, dtype=torch.float32, device=img.device)
-    _abi.call("hg_warp_l1_fwd", H.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h, w,
-              loss.data_ptr(), _stream(stream))
+    ws, hold = _part_ws(B, h, w, img.device, stream)
+    _abi.call("hg_warp_l1_fwd_ws", H.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h, w,
+              loss.data_ptr(), *ws, _stream(stream))
     return loss
 
 
@@ -509,8 +533,9 @@ def hg_warp_l1_bwd(H, img, tgt, grad_loss, stream=None):
     _c(H, "H", torch.float64)
     _c(grad_loss, "grad_loss")
     gH = torch.empty((B, 9), dtype=torch.float64, device=img.device)
-    _abi.call("hg_warp_l1_bwd", H.data_ptr(), img.data_ptr(), tgt.data_ptr(),
-              grad_loss.data_ptr(), B, h, w, gH.data_ptr(), _stream(stream))
+    ws, hold = _part_ws(B, h, w, img.device, stream)
+    _abi.call("hg_warp_l1_bwd_ws", H.data_ptr(), img.data_ptr(), tgt.data_ptr(),
+              grad_loss.data_ptr(), B, h, w, gH.data_ptr(), *ws, _stream(stream))
     return gH
 
 
@@ -589,8 +614,9 @@ def hg_photometric_fwd(offsets, img, tgt, stream=None):
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
     loss = torch.empty(B, dtype=torch.float32, device=img.device)
-    _abi.call("hg_photometric_fwd", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h, w,
-              loss.data_ptr(), _stream(stream))
+    ws, hold = _part_ws(B, h, w, img.device, stream)
+    _abi.call("hg_photometric_fwd_ws", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h, w,
+              loss.data_ptr(), *ws, _stream(stream))
     return loss
 
 
@@ -601,8 +627,9 @@ def hg_photometric_bwd(offsets, img, tgt, grad_loss, stream=None):
     _img3(tgt, "tgt")
     _c(grad_loss, "grad_loss")
     g = torch.empty((B, 4, 2), dtype=torch.float32, device=img.device)
-    _abi.call("hg_photometric_bwd", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(),
-              grad_loss.data_ptr(), B, h, w, g.data_ptr(), _stream(stream))
+    ws, hold = _part_ws(B, h, w, img.device, stream)
+    _abi.call("hg_photometric_bwd_ws", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(),
+              grad_loss.data_ptr(), B, h, w, g.data_ptr(), *ws, _stream(stream))
     return g
 
 
@@ -614,8 +641,9 @@ def hg_photometric_fwd_grad(offsets, img, tgt, stream=None):
     _img3(tgt, "tgt")
     loss = torch.empty(B, dtype=torch.float32, device=img.device)
     g = torch.empty((B, 4, 2), dtype=torch.float32, device=img.device)
-    _abi.call("hg_photometric_fwd_grad", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h,
-              w, loss.data_ptr(), g.data_ptr(), _stream(stream))
+    ws, hold = _part_ws(B, h, w, img.device, stream)
+    _abi.call("hg_photometric_fwd_grad_ws", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h,
+              w, loss.data_ptr(), g.data_ptr(), *ws, _stream(stream))
     return loss, g
 
 
@@ -704,17 +732,29 @@ class Refine:
             raise ValueError("shapes: img, tgt (B, h, w); offsets (B, 4, 2)")
         self.iters, self.step = int(iters), float(step)
         self.loss = torch.empty(self.B, dtype=torch.float32, device=img.device) if with_loss else None
+        n = _abi.lib().hg_refine_ws_bytes(self.B, self.h, self.w)
+        self.ws = torch.empty(n, dtype=torch.uint8, device=img.device) if n else None
+        self._ws_stream = _stream() if n else None
+
+    def _record(self, raw, stream):
+        """Keeps the workspace from being handed out again before work queued on
+        another stream than the one it was allocated on has run."""
+        if self.ws is not None and raw != self._ws_stream:
+            self.ws.record_stream(torch.cuda.current_stream() if stream is None else stream)
 
     def _args(self):
+        ws = (None, 0) if self.ws is None else (self.ws.data_ptr(), self.ws.numel())
         return (self.img.data_ptr(), self.tgt.data_ptr(), self.B, self.h, self.w, self.iters,
                 self.step, self.offsets.data_ptr(),
-                self.loss.data_ptr() if self.loss is not None else None)
+                self.loss.data_ptr() if self.loss is not None else None, *ws)
 
     def run(self, stream=None):
-        _abi.call("hg_refine", *self._args(), _stream(stream))
+        raw = _stream(stream)
+        self._record(raw, stream)
+        _abi.call("hg_refine_ws", *self._args(), raw)
         return self.offsets, self.loss
 
     def graph(self, stream=None):
         h = C.c_void_p()
-        _abi.call("hg_refine_graph_create", *self._args(), _stream(stream), C.byref(h))
+        _abi.call("hg_refine_graph_create_ws", *self._args(), _stream(stream), C.byref(h))
         return Graph(h, self)

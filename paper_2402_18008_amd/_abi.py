@@ -70,6 +70,16 @@ SIGNATURES = {
                                          C.POINTER(vp)]),
     "hg_warp_l1_fwd": (C.c_int, [vp, vp, vp, i32, i32, i32, vp, vp]),
     "hg_warp_l1_bwd": (C.c_int, [vp, vp, vp, vp, i32, i32, i32, vp, vp]),
+    "hg_photometric_ws_bytes": (sz, [i32, i32, i32]),
+    "hg_refine_ws_bytes": (sz, [i32, i32, i32]),
+    "hg_warp_l1_fwd_ws": (C.c_int, [vp, vp, vp, i32, i32, i32, vp, vp, sz, vp]),
+    "hg_warp_l1_bwd_ws": (C.c_int, [vp, vp, vp, vp, i32, i32, i32, vp, vp, sz, vp]),
+    "hg_photometric_fwd_ws": (C.c_int, [vp, vp, vp, i32, i32, i32, vp, vp, sz, vp]),
+    "hg_photometric_bwd_ws": (C.c_int, [vp, vp, vp, vp, i32, i32, i32, vp, vp, sz, vp]),
+    "hg_photometric_fwd_grad_ws": (C.c_int, [vp, vp, vp, i32, i32, i32, vp, vp, vp, sz, vp]),
+    "hg_refine_ws": (C.c_int, [vp, vp, i32, i32, i32, i32, f32, vp, vp, vp, sz, vp]),
+    "hg_refine_graph_create_ws": (C.c_int, [vp, vp, i32, i32, i32, i32, f32, vp, vp, vp, sz, vp,
+                                            C.POINTER(vp)]),
     "hg_warp_store_fwd": (C.c_int, [vp, vp, i32, i32, i32, vp, vp]),
     "hg_l1_fwd": (C.c_int, [vp, vp, i32, i32, i32, vp, vp]),
     "hg_l1_bwd": (C.c_int, [vp, vp, vp, i32, i32, i32, vp, vp]),

@@ -260,15 +260,16 @@ struct PixelWalk {
   int x[kUnroll], y[kUnroll];
   float yf[kUnroll];
   int step_x, step_y, w;
-  __device__ __forceinline__ PixelWalk(int w_) : w(w_) {
+  // first: the workgroup's first pixel (a multiple of NT kUnroll)
+  __device__ __forceinline__ PixelWalk(int w_, int first) : w(w_) {
     constexpr int kStep = NT * kUnroll;
     step_y = kStep / w;
     step_x = kStep % w;
     if (ALIGNED) {
       // one column per thread: pixel threadIdx.x + u NT is NT / w rows below
       // pixel threadIdx.x + (u - 1) NT
-      const int y0 = static_cast<int>(threadIdx.x) / w;
-      const int x0 = static_cast<int>(threadIdx.x) - y0 * w;
+      const int y0 = (first + static_cast<int>(threadIdx.x)) / w;
+      const int x0 = first + static_cast<int>(threadIdx.x) - y0 * w;
       const int dy = NT / w;
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
@@ -279,7 +280,7 @@ struct PixelWalk {
     } else {
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        const int i = static_cast<int>(threadIdx.x) + u * NT;
+        const int i = first + static_cast<int>(threadIdx.x) + u * NT;
         y[u] = i / w;
         x[u] = i % w;
       }
@@ -391,24 +392,34 @@ enum WarpMode {
   kLossGrad = 4,    // loss[b] and dloss[b]/dH in one pass (gl = 1 / (h w))
 };
 
-// One patch b per workgroup; Hb: its 9 entries of H (global or LDS). Writes
-// the loss (kLoss, kLossGrad; thread 0), the warped image (kStore), and dL/dH
-// to gHout (kGrad, kGradStored, kLossGrad; thread 0, 9 doubles).
+// Sums of one workgroup over its pixels: the 9 dL/dG terms, then the loss.
+constexpr int kSums = 10;
+
+// The pixels [first, last) of patch b; Hb: its 9 entries of H (global or LDS).
+// PART = false: the whole patch in one workgroup, which writes the loss
+// (kLoss, kLossGrad; thread 0), the warped image (kStore), and dL/dH to gHout
+// (kGrad, kGradStored, kLossGrad; thread 0, 9 doubles). PART = true: a part of
+// the patch (first a multiple of NT kUnroll, last too or the patch's end); the
+// workgroup's kSums sums go to part (those its MODE computes; thread 0), to be
+// added over the patch's parts by a later kernel.
 // The gradient of the loss through q = G p, position (q0, q1) / q2: with
 // g = dL/dI_w at a pixel (gl sign(r) for the L1 loss, gl a per-patch
 // constant), (a0, a1) = g iq grad I there and iq = 1/q2,
 // dL/dG row 1 += a0 p, row 2 += a1 p, row 3 += -(a0 sx + a1 sy) p.
-template <int MODE, int NT, bool ALIGNED>
+template <int MODE, int NT, bool ALIGNED, bool PART = false>
 __device__ __forceinline__ void warp_block(const double *Hb, const float *__restrict__ img,
                                            const float *__restrict__ tgt, float gl, int h, int w,
                                            int b, float *__restrict__ loss,
-                                           float *__restrict__ warped, double *gHout) {
+                                           float *__restrict__ warped, double *gHout,
+                                           int first = 0, int last = 0,
+                                           double *__restrict__ part = nullptr) {
   constexpr bool GRAD = MODE == kGrad || MODE == kGradStored || MODE == kLossGrad;
   constexpr bool LOSS = MODE == kLoss || MODE == kLossGrad;
   double G[9];
   int e;
   load_G(Hb, G, e);
   const int P = h * w;
+  const int begin = PART ? first : 0, end = PART ? last : P;
   const __amdgpu_buffer_rsrc_t rs = patch_buffer(img + static_cast<int64_t>(b) * P, P);
   // the second stream (target or stored gradient) as a buffer too: indices
   // past the patch (the last loop's tail) read 0
@@ -417,7 +428,7 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
   // float partial sums (folded every kFold iterations) and their double totals:
   // 0..8 the dL/dG terms, 9 the loss. ALIGNED: x is the thread's column, so the
   // x-multiplied sums 0, 3, 6 are x times the sums 2, 5, 8, taken at the fold
-  constexpr int NS = 10;
+  constexpr int NS = kSums;
   float sf[NS];
   double sd[NS];
 #pragma unroll
@@ -425,7 +436,7 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
     sf[k] = 0.0f;
     sd[k] = 0.0;
   }
-  PixelWalk<NT, ALIGNED> pw(w);
+  PixelWalk<NT, ALIGNED> pw(w, begin);
   // ALIGNED: per-thread constant part of q (column x)
   double A[3] = {0.0, 0.0, 0.0};
   const float xcol = static_cast<float>(pw.x[0]);
@@ -471,7 +482,7 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
       const double iq = recip(q2);
       const double sx = q0 * iq, sy = q1 * iq;
       ta[u] = tap_addr(sx, sy, h, w);
-      if (TAIL && i0 + u * NT >= P) ta[u].o0 = ta[u].o1 = kFarOffset;   // past the patch: 0
+      if (TAIL && i0 + u * NT >= end) ta[u].o0 = ta[u].o1 = kFarOffset;   // past the patch: 0
       if (GRAD) {
         sxf[u] = static_cast<float>(sx);
         syf[u] = static_cast<float>(sy);
@@ -490,7 +501,7 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
       const int i = i0 + u * NT;
-      const bool in = !TAIL || i < P;
+      const bool in = !TAIL || i < end;
       float L[4];
       tap_pick(ta[u], raw[u], L);
       const Tap t = tap_eval<GRAD>(ta[u], L);
@@ -533,11 +544,11 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
   // and leave their slots idle while the rest run on a thinner CU. Each wave's
   // priority therefore steps down as it advances (3 in the first quarter of
   // its iterations, 0 in the last), so that waves behind are issued first.
-  const int n_full = P / (NT * kUnroll);
+  const int n_full = (end - begin) / (NT * kUnroll);
   int since = 0, it = 0, prio = 3;
   __builtin_amdgcn_s_setprio(3);
-  int i0 = threadIdx.x;
-  for (; i0 - static_cast<int>(threadIdx.x) + NT * kUnroll <= P; i0 += NT * kUnroll) {
+  int i0 = begin + threadIdx.x;
+  for (; i0 - static_cast<int>(threadIdx.x) + NT * kUnroll <= end; i0 += NT * kUnroll) {
     const int want = 3 - (4 * it) / max(n_full, 1);
     if (want != prio) {
       prio = want;
@@ -553,20 +564,25 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
       since = 0;
     }
   }
-  if (i0 - static_cast<int>(threadIdx.x) < P) iteration(i0, std::true_type());
+  if (i0 - static_cast<int>(threadIdx.x) < end) iteration(i0, std::true_type());
   __builtin_amdgcn_s_setprio(0);
   fold();
   if (LOSS && !GRAD) {
     double s1[1] = {sd[9]}, o1[1];
     block_sum<1, NT>(s1, o1);
-    if (threadIdx.x == 0) loss[b] = static_cast<float>(o1[0] / static_cast<double>(P));
+    if (PART && threadIdx.x == 0) part[kSums - 1] = o1[0];
+    if (!PART && threadIdx.x == 0) loss[b] = static_cast<float>(o1[0] / static_cast<double>(P));
   }
   if (GRAD) {
     double s10[NS], o10[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) s10[k] = sd[k];
     block_sum<NS, NT>(s10, o10);
-    if (threadIdx.x == 0) {
+    if (PART && threadIdx.x == 0) {
+#pragma unroll
+      for (int k = 0; k < (LOSS ? NS : NS - 1); ++k) part[k] = o10[k];
+    }
+    if (!PART && threadIdx.x == 0) {
       if (LOSS) loss[b] = static_cast<float>(o10[9] / static_cast<double>(P));
       adjugate_backward(Hb, o10, e, gHout);
     }
@@ -661,6 +677,172 @@ __global__ __launch_bounds__(NT, 4) void photo_fwd_grad_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) grad_unit[8 * b + i] = static_cast<float>(g[i]);
   }
+}
+
+// ---- one patch over several workgroups --------------------------------------
+// A batch with fewer patches than the chip has room for leaves compute units
+// idle with one workgroup per patch (24 patches of 211 x 317 ran on 24 of the
+// 256 units: forward 28.1 us, backward 38.7 us, six steps 263 us; cut 9.8,
+// 12.0 and 77 us). Its patches are cut into S parts of whole
+// iterations instead (split_parts): workgroup j takes part j / B of patch
+// j % B (so that the parts of a patch are dispatched B apart, on one XCD and
+// its L2 when B is a multiple of 8), and writes its kSums double sums to
+// part[patch][part]. What follows the sums (the reverse mode, the mean) runs
+// in a kernel of one wave per patch, or, inside a refinement, in the prologue
+// of the next step. The parts are added in a fixed order, so the result does
+// not depend on the order in which workgroups finish.
+constexpr int kPartThreads = 256;
+constexpr int kPartPixels = kPartThreads * kUnroll;   // one iteration
+
+struct PartShape {
+  int B, S, per;   // patches, parts per patch, iterations per part
+};
+
+__device__ __forceinline__ void part_range(const PartShape &ps, int P, int &b, int &s, int &first,
+                                           int &last) {
+  s = static_cast<int>(blockIdx.x) / ps.B;
+  b = static_cast<int>(blockIdx.x) - s * ps.B;
+  first = s * ps.per * kPartPixels;
+  last = min(first + ps.per * kPartPixels, P);
+}
+
+// Sums of a patch's S parts (kSums doubles each), by one wave: lane k + 10 r
+// (r < 6) adds the parts r, r + 6, ... of value k, then every lane adds the
+// six partial sums of all values in order. Result in every lane.
+__device__ __forceinline__ void sum_parts(const double *__restrict__ part, int S, double *sum) {
+  constexpr int kRows = 6;
+  const int lane = threadIdx.x & 63;
+  const int k = lane % kSums, r = lane / kSums;
+  double x = 0.0;
+  if (r < kRows)
+    for (int s = r; s < S; s += kRows) x += part[s * kSums + k];
+#pragma unroll
+  for (int j = 0; j < kSums; ++j) {
+    double v = __shfl(x, j);
+#pragma unroll
+    for (int i = 1; i < kRows; ++i) v += __shfl(x, j + kSums * i);
+    sum[j] = v;
+  }
+}
+
+// dL/dH (9) from the summed dL/dG terms and H.
+__device__ __forceinline__ void grad_from_sums(const double *Hb, const double *sum, double *gH) {
+  double G[9];
+  const int e = adjugate_scaled(Hb, G);
+  adjugate_backward(Hb, sum, e, gH);
+}
+
+// Parts of a warp pass. RECT: H from the rectangle and offsets, else the given
+// H (B x 9). gl as in warp_kernel / photo_bwd_kernel / photo_fwd_grad_kernel.
+template <int MODE, bool RECT, bool ALIGNED>
+__global__ __launch_bounds__(kPartThreads, 4) void part_kernel(
+    PartShape ps, const double *__restrict__ H, const float *__restrict__ off,
+    const float *__restrict__ img, const float *__restrict__ tgt,
+    const float *__restrict__ grad_loss, int h, int w, RectArgs ra, double *__restrict__ part) {
+  __shared__ double Hs[9];
+  int b, s, first, last;
+  part_range(ps, h * w, b, s, first, last);
+  if (RECT) rect_to_lds(off + 8 * b, ra, Hs);
+  const float gl = MODE == kGrad       ? static_cast<float>(static_cast<double>(grad_loss[b]) /
+                                                            static_cast<double>(h * w))
+                   : MODE == kLossGrad ? static_cast<float>(1.0 / static_cast<double>(h * w))
+                                       : 0.0f;
+  warp_block<MODE, kPartThreads, ALIGNED, true>(
+      RECT ? Hs : H + 9 * b, img, tgt, gl, h, w, b, nullptr, nullptr, nullptr, first, last,
+      part + (static_cast<int64_t>(b) * ps.S + s) * kSums);
+}
+
+// After part_kernel: one wave per patch adds its parts and writes the loss
+// and the gradient (RECT: of the offsets, 8 floats; else of H, 9 doubles).
+template <int MODE, bool RECT>
+__global__ __launch_bounds__(64) void part_finish_kernel(
+    PartShape ps, const double *__restrict__ H, const float *__restrict__ off, int P, RectArgs ra,
+    const double *__restrict__ part, float *__restrict__ loss, float *__restrict__ goff,
+    double *__restrict__ gHout) {
+  const int b = blockIdx.x;
+  double sum[kSums];
+  sum_parts(part + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
+  if (threadIdx.x != 0) return;
+  if (MODE == kLoss || MODE == kLossGrad)
+    loss[b] = static_cast<float>(sum[kSums - 1] / static_cast<double>(P));
+  if (MODE == kLoss) return;
+  double gH[9];
+  if (RECT) {
+    double Hd[9], g[8];
+    rect_h(off + 8 * b, ra, Hd);
+    grad_from_sums(Hd, sum, gH);
+    rect_h_vjp(off + 8 * b, ra, gH, g);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) goff[8 * b + i] = static_cast<float>(g[i]);
+  } else {
+    grad_from_sums(H + 9 * b, sum, gH);
+#pragma unroll
+    for (int i = 0; i < 9; ++i) gHout[9 * b + i] = gH[i];
+  }
+}
+
+// One refinement step (LOSS = false) or the loss after the last one, over
+// parts. Its prologue finishes the step before: with prev (that step's parts;
+// NULL before the first step) every workgroup of a patch adds them, takes the
+// gradient at off_in and steps, off = off_in - step * gradient; the part 0
+// workgroup stores it in off_out. Offsets and parts alternate between two
+// buffers, since the other workgroups of a patch may still be reading.
+template <bool LOSS, bool ALIGNED>
+__global__ __launch_bounds__(kPartThreads, 4) void refine_part_kernel(
+    PartShape ps, const float *__restrict__ off_in, const double *__restrict__ prev,
+    const float *__restrict__ img, const float *__restrict__ tgt, int h, int w, RectArgs ra,
+    float step, float *__restrict__ off_out, double *__restrict__ part) {
+  __shared__ double Hs[9];
+  int b, s, first, last;
+  part_range(ps, h * w, b, s, first, last);
+  if (threadIdx.x < 64) {
+    double sum[kSums];
+    if (prev) sum_parts(prev + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
+    if (threadIdx.x == 0) {
+      float o[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = off_in[8 * b + i];
+      if (prev) {
+        double Hd[9], gH[9], g[8];
+        rect_h(o, ra, Hd);
+        grad_from_sums(Hd, sum, gH);
+        rect_h_vjp(o, ra, gH, g);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] = o[i] - step * static_cast<float>(g[i]);
+      }
+      if (s == 0 && off_out)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) off_out[8 * b + i] = o[i];
+      double hh[9];
+      rect_h(o, ra, hh);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) Hs[i] = hh[i];
+    }
+  }
+  const float gl = static_cast<float>(1.0 / static_cast<double>(h * w));
+  warp_block<LOSS ? kLoss : kGrad, kPartThreads, ALIGNED, true>(
+      Hs, img, tgt, gl, h, w, b, nullptr, nullptr, nullptr, first, last,
+      part + (static_cast<int64_t>(b) * ps.S + s) * kSums);
+}
+
+// The last step of a refinement without a loss pass: off = off_in - step *
+// gradient, one wave per patch.
+__global__ __launch_bounds__(64) void refine_last_kernel(PartShape ps,
+                                                         const float *__restrict__ off_in,
+                                                         const double *__restrict__ prev,
+                                                         RectArgs ra, float step,
+                                                         float *__restrict__ off_out) {
+  const int b = blockIdx.x;
+  double sum[kSums];
+  sum_parts(prev + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
+  if (threadIdx.x != 0) return;
+  double Hd[9], gH[9], g[8];
+  rect_h(off_in + 8 * b, ra, Hd);
+  grad_from_sums(Hd, sum, gH);
+  rect_h_vjp(off_in + 8 * b, ra, gH, g);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    off_out[8 * b + i] = off_in[8 * b + i] - step * static_cast<float>(g[i]);
 }
 
 // out[b, k] = grad_loss[b] * grad_unit[b, k] (8 per patch).
@@ -825,7 +1007,118 @@ static void with_shape(int B, int w, F &&f) {
   go(std::integral_constant<int, 256>());
 }
 
-static int launch_refine(const RefineArgs &a, hipStream_t s) {
+// Parts per patch: as many as give about kPartGroups workgroups over the batch,
+// each at least one whole iteration. Cutting pays from 8 iterations a patch
+// on, and up to kPartMaxBatch patches: below 8 the second launch costs more
+// than the parts save (16 patches of 64 x 64, forward: 4.9 us whole, 6.5 us
+// cut), and with more patches the whole form fills the chip (128 x 128,
+// forward + backward in one pass: 128 patches 11.6 us whole, 11.3 us cut; 192
+// patches 12.4 and 12.5 us; 64 patches 11.3 and 8.9 us; 24 patches of
+// 211 x 317 38.4 and 12.9 us). Fewer workgroups leave compute units idle, more
+// repeat the serial prologue (24 of 211 x 317: 13.8, 13.0, 12.9 and 13.1 us for
+// 256, 512, 768 and 1024; 64 of 256 x 256: 18.3, 14.9, 14.9 and 15.8 us).
+constexpr int kPartGroups = 768;
+constexpr int kPartMaxBatch = 128;
+constexpr int kPartMinIters = 8;
+static PartShape split_parts(int B, int h, int w) {
+  PartShape ps = {B, 1, 0};
+  const int iters = (h * w + kPartPixels - 1) / kPartPixels;
+  if (B < 1 || B > kPartMaxBatch || iters < kPartMinIters) return ps;
+  const int want = std::min(iters, (kPartGroups + B - 1) / B);
+  ps.per = (iters + want - 1) / want;
+  ps.S = (iters + ps.per - 1) / ps.per;
+  return ps;
+}
+
+static size_t part_bytes(const PartShape &ps) {
+  return sizeof(double) * kSums * static_cast<size_t>(ps.B) * ps.S;
+}
+
+// Workspace of hg_refine_ws: two sets of parts and two of offsets.
+static size_t refine_bytes(const PartShape &ps) {
+  return 2 * (part_bytes(ps) + 8 * sizeof(float) * static_cast<size_t>(ps.B));
+}
+
+// The split shape to use with workspace ws (NULL: one workgroup per patch).
+static int use_parts(int B, int h, int w, const void *ws, size_t ws_bytes, bool refine,
+                     const char *fn, PartShape &ps) {
+  ps = {B, 1, 0};
+  if (!ws) return HG_OK;
+  ps = split_parts(B, h, w);
+  const size_t need = ps.S == 1 ? 0 : refine ? refine_bytes(ps) : part_bytes(ps);
+  if (ws_bytes < need)
+    return fail(HG_EWORKSPACE, "%s: workspace of %zu bytes needed, %zu given", fn, need, ws_bytes);
+  HG_REQUIRE(aligned(ws, 16), "%s: workspace must be 16-byte aligned", fn);
+  return HG_OK;
+}
+
+template <typename F>
+static void with_aligned(int w, F &&f) {
+  if (kPartThreads % w == 0)
+    f(std::true_type());
+  else
+    f(std::false_type());
+}
+
+// A split warp pass and its finish (the parts go to ws).
+template <int MODE, bool RECT>
+static int launch_parts(const PartShape &ps, const double *H, const float *off, const float *img,
+                        const float *tgt, const float *grad_loss, int h, int w, void *ws,
+                        float *loss, float *goff, double *gH, hipStream_t s) {
+  const RectArgs ra = RECT ? patch_rect(h, w) : RectArgs{};
+  double *part = static_cast<double *>(ws);
+  with_aligned(w, [&](auto al) {
+    hipLaunchKernelGGL((part_kernel<MODE, RECT, decltype(al)::value>), dim3(ps.B * ps.S),
+                       dim3(kPartThreads), 0, s, ps, H, off, img, tgt, grad_loss, h, w, ra, part);
+  });
+  if (int st = launched("part_kernel")) return st;
+  hipLaunchKernelGGL((part_finish_kernel<MODE, RECT>), dim3(ps.B), dim3(64), 0, s, ps, H, off,
+                     h * w, ra, part, loss, goff, gH);
+  return launched("part_finish_kernel");
+}
+
+// The refinement over parts: one launch per step (each finishes the step
+// before), then the loss (two launches) or the last step alone.
+static int launch_refine_parts(const RefineArgs &a, const PartShape &ps, void *ws,
+                               hipStream_t s) {
+  const RectArgs ra = patch_rect(a.h, a.w);
+  double *part[2];
+  float *off[2];
+  part[0] = static_cast<double *>(ws);
+  part[1] = part[0] + part_bytes(ps) / sizeof(double);
+  off[0] = reinterpret_cast<float *>(part[1] + part_bytes(ps) / sizeof(double));
+  off[1] = off[0] + 8 * static_cast<size_t>(ps.B);
+  const float *from = a.off;
+  const double *prev = nullptr;
+  for (int it = 0; it < a.iters; ++it) {
+    with_aligned(a.w, [&](auto al) {
+      hipLaunchKernelGGL((refine_part_kernel<false, decltype(al)::value>), dim3(ps.B * ps.S),
+                         dim3(kPartThreads), 0, s, ps, from, prev, a.img, a.tgt, a.h, a.w, ra,
+                         a.step, off[it & 1], part[it & 1]);
+    });
+    if (int st = launched("refine_part_kernel")) return st;
+    from = off[it & 1];
+    prev = part[it & 1];
+  }
+  if (!a.loss) {
+    if (a.iters == 0) return HG_OK;
+    hipLaunchKernelGGL(refine_last_kernel, dim3(ps.B), dim3(64), 0, s, ps, from, prev, ra, a.step,
+                       a.off);
+    return launched("refine_last_kernel");
+  }
+  with_aligned(a.w, [&](auto al) {
+    hipLaunchKernelGGL((refine_part_kernel<true, decltype(al)::value>), dim3(ps.B * ps.S),
+                       dim3(kPartThreads), 0, s, ps, from, prev, a.img, a.tgt, a.h, a.w, ra, a.step,
+                       a.iters ? a.off : nullptr, part[a.iters & 1]);
+  });
+  if (int st = launched("refine_part_kernel<loss>")) return st;
+  hipLaunchKernelGGL((part_finish_kernel<kLoss, true>), dim3(ps.B), dim3(64), 0, s, ps, nullptr,
+                     nullptr, a.h * a.w, ra, part[a.iters & 1], a.loss, nullptr, nullptr);
+  return launched("part_finish_kernel<loss>");
+}
+
+static int launch_refine(const RefineArgs &a, const PartShape &ps, void *ws, hipStream_t s) {
+  if (ps.S > 1) return launch_refine_parts(a, ps, ws, s);
   const RectArgs ra = patch_rect(a.h, a.w);
   for (int it = 0; it < a.iters; ++it) {
     with_shape<512, 4096>(a.B, a.w, [&](auto nt, auto al) {
@@ -932,12 +1225,16 @@ extern "C" int hg_aca_bwd(const float *src, const float *dst, const double *grad
   return launched("aca_bwd_kernel");
 }
 
-extern "C" int hg_warp_l1_fwd(const double *H, const float *img, const float *tgt, int32_t B,
-                              int32_t h, int32_t w, float *loss, void *stream) {
+extern "C" int hg_warp_l1_fwd_ws(const double *H, const float *img, const float *tgt, int32_t B,
+                              int32_t h, int32_t w, float *loss, void *ws, size_t ws_bytes, void *stream) {
   clear_error();
   if (int st = check_img(img, tgt, B, h, w, "hg_warp_l1_fwd")) return st;
   if (B == 0) return HG_OK;
   HG_REQUIRE(H && loss, "hg_warp_l1_fwd: NULL pointer");
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_warp_l1_fwd", ps)) return st;
+  if (ps.S > 1)
+    return launch_parts<kLoss, false>(ps, H, nullptr, img, tgt, nullptr, h, w, ws, loss, nullptr, nullptr, as_stream(stream));
   with_shape(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
@@ -947,13 +1244,22 @@ extern "C" int hg_warp_l1_fwd(const double *H, const float *img, const float *tg
   return launched("warp_kernel<loss>");
 }
 
-extern "C" int hg_warp_l1_bwd(const double *H, const float *img, const float *tgt,
+extern "C" int hg_warp_l1_fwd(const double *H, const float *img, const float *tgt, int32_t B,
+                              int32_t h, int32_t w, float *loss, void *stream) {
+  return hg_warp_l1_fwd_ws(H, img, tgt, B, h, w, loss, nullptr, 0, stream);
+}
+
+extern "C" int hg_warp_l1_bwd_ws(const double *H, const float *img, const float *tgt,
                               const float *grad_loss, int32_t B, int32_t h, int32_t w,
-                              double *grad_H, void *stream) {
+                              double *grad_H, void *ws, size_t ws_bytes, void *stream) {
   clear_error();
   if (int st = check_img(img, tgt, B, h, w, "hg_warp_l1_bwd")) return st;
   if (B == 0) return HG_OK;
   HG_REQUIRE(H && grad_loss && grad_H, "hg_warp_l1_bwd: NULL pointer");
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_warp_l1_bwd", ps)) return st;
+  if (ps.S > 1)
+    return launch_parts<kGrad, false>(ps, H, nullptr, img, tgt, grad_loss, h, w, ws, nullptr, nullptr, grad_H, as_stream(stream));
   with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
@@ -961,6 +1267,12 @@ extern "C" int hg_warp_l1_bwd(const double *H, const float *img, const float *tg
                        img, tgt, grad_loss, h, w, nullptr, nullptr, grad_H);
   });
   return launched("warp_kernel<grad>");
+}
+
+extern "C" int hg_warp_l1_bwd(const double *H, const float *img, const float *tgt,
+                              const float *grad_loss, int32_t B, int32_t h, int32_t w,
+                              double *grad_H, void *stream) {
+  return hg_warp_l1_bwd_ws(H, img, tgt, grad_loss, B, h, w, grad_H, nullptr, 0, stream);
 }
 
 extern "C" int hg_warp_store_fwd(const double *H, const float *img, int32_t B, int32_t h,
@@ -1017,13 +1329,17 @@ extern "C" int hg_warp_bwd_from_grad(const double *H, const float *img, const fl
   return launched("warp_kernel<grad_stored>");
 }
 
-extern "C" int hg_photometric_fwd(const float *offsets, const float *img, const float *tgt,
-                                  int32_t B, int32_t h, int32_t w, float *loss, void *stream) {
+extern "C" int hg_photometric_fwd_ws(const float *offsets, const float *img, const float *tgt,
+                                  int32_t B, int32_t h, int32_t w, float *loss, void *ws, size_t ws_bytes, void *stream) {
   clear_error();
   if (int st = check_img(img, tgt, B, h, w, "hg_photometric_fwd")) return st;
   HG_REQUIRE(h >= 2 && w >= 2, "hg_photometric_fwd: patches need h, w >= 2");
   if (B == 0) return HG_OK;
   HG_REQUIRE(offsets && loss, "hg_photometric_fwd: NULL offsets or loss");
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_fwd", ps)) return st;
+  if (ps.S > 1)
+    return launch_parts<kLoss, true>(ps, nullptr, offsets, img, tgt, nullptr, h, w, ws, loss, nullptr, nullptr, as_stream(stream));
   with_shape(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
@@ -1033,14 +1349,23 @@ extern "C" int hg_photometric_fwd(const float *offsets, const float *img, const 
   return launched("photo_fwd_kernel");
 }
 
-extern "C" int hg_photometric_bwd(const float *offsets, const float *img, const float *tgt,
+extern "C" int hg_photometric_fwd(const float *offsets, const float *img, const float *tgt,
+                                  int32_t B, int32_t h, int32_t w, float *loss, void *stream) {
+  return hg_photometric_fwd_ws(offsets, img, tgt, B, h, w, loss, nullptr, 0, stream);
+}
+
+extern "C" int hg_photometric_bwd_ws(const float *offsets, const float *img, const float *tgt,
                                   const float *grad_loss, int32_t B, int32_t h, int32_t w,
-                                  float *grad_offsets, void *stream) {
+                                  float *grad_offsets, void *ws, size_t ws_bytes, void *stream) {
   clear_error();
   if (int st = check_img(img, tgt, B, h, w, "hg_photometric_bwd")) return st;
   HG_REQUIRE(h >= 2 && w >= 2, "hg_photometric_bwd: patches need h, w >= 2");
   if (B == 0) return HG_OK;
   HG_REQUIRE(offsets && grad_loss && grad_offsets, "hg_photometric_bwd: NULL pointer");
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_bwd", ps)) return st;
+  if (ps.S > 1)
+    return launch_parts<kGrad, true>(ps, nullptr, offsets, img, tgt, grad_loss, h, w, ws, nullptr, grad_offsets, nullptr, as_stream(stream));
   with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
@@ -1051,14 +1376,24 @@ extern "C" int hg_photometric_bwd(const float *offsets, const float *img, const 
   return launched("photo_bwd_kernel");
 }
 
-extern "C" int hg_photometric_fwd_grad(const float *offsets, const float *img, const float *tgt,
+extern "C" int hg_photometric_bwd(const float *offsets, const float *img, const float *tgt,
+                                  const float *grad_loss, int32_t B, int32_t h, int32_t w,
+                                  float *grad_offsets, void *stream) {
+  return hg_photometric_bwd_ws(offsets, img, tgt, grad_loss, B, h, w, grad_offsets, nullptr, 0, stream);
+}
+
+extern "C" int hg_photometric_fwd_grad_ws(const float *offsets, const float *img, const float *tgt,
                                        int32_t B, int32_t h, int32_t w, float *loss,
-                                       float *grad_unit, void *stream) {
+                                       float *grad_unit, void *ws, size_t ws_bytes, void *stream) {
   clear_error();
   if (int st = check_img(img, tgt, B, h, w, "hg_photometric_fwd_grad")) return st;
   HG_REQUIRE(h >= 2 && w >= 2, "hg_photometric_fwd_grad: patches need h, w >= 2");
   if (B == 0) return HG_OK;
   HG_REQUIRE(offsets && loss && grad_unit, "hg_photometric_fwd_grad: NULL pointer");
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_fwd_grad", ps)) return st;
+  if (ps.S > 1)
+    return launch_parts<kLossGrad, true>(ps, nullptr, offsets, img, tgt, nullptr, h, w, ws, loss, grad_unit, nullptr, as_stream(stream));
   with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
@@ -1066,6 +1401,12 @@ extern "C" int hg_photometric_fwd_grad(const float *offsets, const float *img, c
                        offsets, img, tgt, h, w, patch_rect(h, w), loss, grad_unit);
   });
   return launched("photo_fwd_grad_kernel");
+}
+
+extern "C" int hg_photometric_fwd_grad(const float *offsets, const float *img, const float *tgt,
+                                       int32_t B, int32_t h, int32_t w, float *loss,
+                                       float *grad_unit, void *stream) {
+  return hg_photometric_fwd_grad_ws(offsets, img, tgt, B, h, w, loss, grad_unit, nullptr, 0, stream);
 }
 
 extern "C" int hg_scale_grad(const float *grad_unit, const float *grad_loss, int32_t B,
@@ -1080,19 +1421,40 @@ extern "C" int hg_scale_grad(const float *grad_unit, const float *grad_loss, int
   return launched("scale_grad_kernel");
 }
 
-extern "C" int hg_refine(const float *img, const float *tgt, int32_t B, int32_t h, int32_t w,
-                         int32_t iters, float step, float *offsets, float *loss, void *stream) {
+extern "C" size_t hg_photometric_ws_bytes(int32_t B, int32_t h, int32_t w) {
+  if (B < 1 || h < 1 || w < 1 || static_cast<int64_t>(h) * w > (int64_t(1) << 29)) return 0;
+  const PartShape ps = split_parts(B, h, w);
+  return ps.S > 1 ? part_bytes(ps) : 0;
+}
+
+extern "C" size_t hg_refine_ws_bytes(int32_t B, int32_t h, int32_t w) {
+  if (B < 1 || h < 1 || w < 1 || static_cast<int64_t>(h) * w > (int64_t(1) << 29)) return 0;
+  const PartShape ps = split_parts(B, h, w);
+  return ps.S > 1 ? refine_bytes(ps) : 0;
+}
+
+extern "C" int hg_refine_ws(const float *img, const float *tgt, int32_t B, int32_t h, int32_t w,
+                            int32_t iters, float step, float *offsets, float *loss, void *ws,
+                            size_t ws_bytes, void *stream) {
   clear_error();
   RefineArgs a;
   if (int st = make_refine(img, tgt, B, h, w, iters, step, offsets, loss, "hg_refine", a))
     return st;
   if (B == 0) return HG_OK;
-  return launch_refine(a, as_stream(stream));
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, true, "hg_refine", ps)) return st;
+  return launch_refine(a, ps, ws, as_stream(stream));
 }
 
-extern "C" int hg_refine_graph_create(const float *img, const float *tgt, int32_t B, int32_t h,
-                                      int32_t w, int32_t iters, float step, float *offsets,
-                                      float *loss, void *stream, hg_graph **out) {
+extern "C" int hg_refine(const float *img, const float *tgt, int32_t B, int32_t h, int32_t w,
+                         int32_t iters, float step, float *offsets, float *loss, void *stream) {
+  return hg_refine_ws(img, tgt, B, h, w, iters, step, offsets, loss, nullptr, 0, stream);
+}
+
+extern "C" int hg_refine_graph_create_ws(const float *img, const float *tgt, int32_t B, int32_t h,
+                                         int32_t w, int32_t iters, float step, float *offsets,
+                                         float *loss, void *ws, size_t ws_bytes, void *stream,
+                                         hg_graph **out) {
   clear_error();
   HG_REQUIRE(out, "hg_refine_graph_create: NULL out");
   *out = nullptr;
@@ -1101,5 +1463,15 @@ extern "C" int hg_refine_graph_create(const float *img, const float *tgt, int32_
                            "hg_refine_graph_create", a))
     return st;
   HG_REQUIRE(B > 0, "hg_refine_graph_create: B must be > 0");
-  return capture_graph(stream, [&](hipStream_t cap) { return launch_refine(a, cap); }, out);
+  PartShape ps;
+  if (int st = use_parts(B, h, w, ws, ws_bytes, true, "hg_refine_graph_create", ps)) return st;
+  return capture_graph(stream, [&](hipStream_t cap) { return launch_refine(a, ps, ws, cap); },
+                       out);
+}
+
+extern "C" int hg_refine_graph_create(const float *img, const float *tgt, int32_t B, int32_t h,
+                                      int32_t w, int32_t iters, float step, float *offsets,
+                                      float *loss, void *stream, hg_graph **out) {
+  return hg_refine_graph_create_ws(img, tgt, B, h, w, iters, step, offsets, loss, nullptr, 0,
+                                   stream, out);
 }
