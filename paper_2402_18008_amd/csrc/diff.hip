@@ -24,60 +24,121 @@ namespace hg {
 
 constexpr int kDiffThreads = 256;
 
-// A rectangle with upper-left (x0, y0), width w and aspect ratio r = width /
-// height, as ACA's source points M N P Q = TL, TR, BL, BR.
+// A rectangle with corners (x0, y0) .. (x1, y1), as ACA's source points
+// M N P Q = TL, TR, BL, BR, and the constants its sides give (f = the doubled
+// triangle area (x1 - x0)(y1 - y0); set up on the host).
 struct RectArgs {
-  double x0, y0, w, r;
+  double x0, y0, x1, y1;
+  double a, b, f;   // width, height, a b
 };
 
-__device__ __forceinline__ void rect_source(const RectArgs &ra, double s[8]) {
-  const double x1 = ra.x0 + ra.w, y1 = ra.y0 + ra.w / ra.r;
-  s[0] = ra.x0;
-  s[1] = ra.y0;
-  s[2] = x1;
-  s[3] = ra.y0;
-  s[4] = ra.x0;
-  s[5] = y1;
-  s[6] = x1;
-  s[7] = y1;
-}
-
 // Target points M N P Q = source corners + offsets (offset order TL TR BR BL).
-__device__ __forceinline__ void rect_target(const float *o, const double s[8], double d[8]) {
-  d[0] = s[0] + static_cast<double>(o[0]);
-  d[1] = s[1] + static_cast<double>(o[1]);
-  d[2] = s[2] + static_cast<double>(o[2]);
-  d[3] = s[3] + static_cast<double>(o[3]);
-  d[6] = s[6] + static_cast<double>(o[4]);
-  d[7] = s[7] + static_cast<double>(o[5]);
-  d[4] = s[4] + static_cast<double>(o[6]);
-  d[5] = s[5] + static_cast<double>(o[7]);
+__device__ __forceinline__ void rect_target(const float *o, const RectArgs &ra, double d[8]) {
+  d[0] = ra.x0 + static_cast<double>(o[0]);
+  d[1] = ra.y0 + static_cast<double>(o[1]);
+  d[2] = ra.x1 + static_cast<double>(o[2]);
+  d[3] = ra.y0 + static_cast<double>(o[3]);
+  d[6] = ra.x1 + static_cast<double>(o[4]);
+  d[7] = ra.y1 + static_cast<double>(o[5]);
+  d[4] = ra.x0 + static_cast<double>(o[6]);
+  d[5] = ra.y1 + static_cast<double>(o[7]);
 }
 
-// H (row-major, ACA's own scale) of one patch from its offsets.
+// Target-side quantities of ACA: difference vectors from M, their areas and
+// the core's entries for a rectangular source, whose areas are Q3.x = Q3.y =
+// f_A1 = f and t1 = -f.
+struct RectCore {
+  double MNx, MNy, MPx, MPy, MQx, MQy, fA2, Q4x, Q4y, t2, c11, c22, c33;
+};
+
+__device__ __forceinline__ RectCore rect_core(const double d[8], double f) {
+  RectCore c;
+  c.MNx = d[2] - d[0];
+  c.MNy = d[3] - d[1];
+  c.MPx = d[4] - d[0];
+  c.MPy = d[5] - d[1];
+  c.MQx = d[6] - d[0];
+  c.MQy = d[7] - d[1];
+  c.fA2 = c.MNx * c.MPy - c.MNy * c.MPx;
+  c.Q4x = c.MQx * c.MPy - c.MQy * c.MPx;
+  c.Q4y = c.MNx * c.MQy - c.MNy * c.MQx;
+  c.t2 = c.fA2 - c.Q4x - c.Q4y;
+  const double tf = -f * f;
+  c.c11 = tf * c.Q4x;
+  c.c22 = tf * c.Q4y;
+  c.c33 = c.t2 * f * f;
+  return c;
+}
+
+// H (row-major, ACA's own scale) of one patch from its offsets: aca_solve in
+// its operation order with the source side's zeros and constants left out
+// (MN1 = (a, 0), MP1 = (0, b)), about half of its operations. One lane runs
+// this ahead of a workgroup's pixels, so its length is latency.
 __device__ __forceinline__ void rect_h(const float *o, const RectArgs &ra, double H[9]) {
-  double s[8], d[8];
-  rect_source(ra, s);
-  rect_target(o, s, d);
-  (void)aca_solve(s, d, H);
+  double d[8];
+  rect_target(o, ra, d);
+  const RectCore c = rect_core(d, ra.f);
+  const double mx = d[0] * c.c33, my = d[1] * c.c33;
+  const double L[3][3] = {{d[2] * c.c11 - mx, d[4] * c.c22 - mx, mx},
+                          {d[3] * c.c11 - my, d[5] * c.c22 - my, my},
+                          {c.c11 - c.c33, c.c22 - c.c33, c.c33}};
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const double h0 = L[i][0] * ra.b, h1 = L[i][1] * ra.a;
+    H[3 * i + 0] = h0;
+    H[3 * i + 1] = h1;
+    H[3 * i + 2] = L[i][2] * ra.f - (h0 * ra.x0 + h1 * ra.y0);
+  }
 }
 
 // dL/d offsets (order TL TR BR BL) from dL/dH, through ACA's reverse mode
-// with respect to the target points.
+// with respect to the target points: aca_vjp's steps for a rectangular source.
 __device__ __forceinline__ void rect_h_vjp(const float *o, const RectArgs &ra, const double gH[9],
                                            double g[8]) {
-  double s[8], d[8], gs[8], gd[8];
-  rect_source(ra, s);
-  rect_target(o, s, d);
-  aca_vjp(s, d, gH, gs, gd);
-  g[0] = gd[0];
-  g[1] = gd[1];
-  g[2] = gd[2];
-  g[3] = gd[3];
-  g[4] = gd[6];
-  g[5] = gd[7];
-  g[6] = gd[4];
-  g[7] = gd[5];
+  double d[8];
+  rect_target(o, ra, d);
+  const RectCore c = rect_core(d, ra.f);
+  double gL[3][3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const double g2 = gH[3 * i + 2];
+    gL[i][0] = (gH[3 * i + 0] - g2 * ra.x0) * ra.b;
+    gL[i][1] = (gH[3 * i + 1] - g2 * ra.y0) * ra.a;
+    gL[i][2] = g2 * ra.f;
+  }
+  // L = H_A2^-1 H_C
+  const double gmx = gL[0][2] - gL[0][0] - gL[0][1];
+  const double gmy = gL[1][2] - gL[1][0] - gL[1][1];
+  const double gc11 = gL[0][0] * d[2] + gL[1][0] * d[3] + gL[2][0];
+  const double gc22 = gL[0][1] * d[4] + gL[1][1] * d[5] + gL[2][1];
+  const double gc33 = gL[2][2] - gL[2][0] - gL[2][1] + gmx * d[0] + gmy * d[1];
+  // core
+  const double tf = -ra.f * ra.f;
+  const double gt2 = gc33 * ra.f * ra.f;
+  const double gQ4x = gc11 * tf - gt2;
+  const double gQ4y = gc22 * tf - gt2;
+  // signed areas and difference vectors
+  const double gMNx = gt2 * c.MPy + gQ4y * c.MQy;
+  const double gMNy = -gt2 * c.MPx - gQ4y * c.MQx;
+  const double gMPx = -gt2 * c.MNy - gQ4x * c.MQy;
+  const double gMPy = gt2 * c.MNx + gQ4x * c.MQx;
+  const double gMQx = gQ4x * c.MPy - gQ4y * c.MNy;
+  const double gMQy = gQ4y * c.MNx - gQ4x * c.MPx;
+  g[0] = gmx * c.c33 - (gMNx + gMPx + gMQx);
+  g[1] = gmy * c.c33 - (gMNy + gMPy + gMQy);
+  g[2] = gL[0][0] * c.c11 + gMNx;
+  g[3] = gL[1][0] * c.c11 + gMNy;
+  g[4] = gMQx;
+  g[5] = gMQy;
+  g[6] = gL[0][1] * c.c22 + gMPx;
+  g[7] = gL[1][1] * c.c22 + gMPy;
+}
+
+// The wave that does a workgroup's serial work (ACA, the adjugate, the reverse
+// mode): a different one for workgroups that share a compute unit (256 apart
+// in dispatch order on 256 units), since equal waves of them share a SIMD.
+__device__ __forceinline__ int lead_thread() {
+  return static_cast<int>((blockIdx.x >> 8) & 3u) * 64;
 }
 
 __global__ void rect_fwd_kernel(const float *__restrict__ off, int B, RectArgs ra,
@@ -310,13 +371,13 @@ struct PixelWalk {
 };
 
 // Workgroup (NT threads) sum of NV per-thread partials, in double. Result valid
-// in thread 0. The partials go through LDS: lane (k, r) of the first NV x 16
+// in thread lead. The partials go through LDS: lane (k, r) of the first NV x 16
 // threads adds the partials r, r + 16, r + 32, ... of value k in that order,
 // then the 16 lanes of value k (one DPP row) add their sums in row order. A
 // fixed order, so the result is deterministic; the DPP work is one row scan
 // per value instead of one per value and thread row.
 template <int NV, int NT>
-__device__ __forceinline__ void block_sum(const double (&v)[NV], double (&out)[NV]) {
+__device__ __forceinline__ void block_sum(const double (&v)[NV], double (&out)[NV], int lead) {
   constexpr int kParts = 16;
   static_assert(NV * kParts <= NT && NT % kParts == 0, "16 lanes per value");
   __shared__ double part[NV][NT];
@@ -334,7 +395,7 @@ __device__ __forceinline__ void block_sum(const double (&v)[NV], double (&out)[N
     if (r == kParts - 1) tot[k] = x;
   }
   __syncthreads();
-  if (t == 0) {
+  if (t == lead) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) out[k] = tot[k];
   }
@@ -345,7 +406,7 @@ __device__ __forceinline__ void block_sum(const double (&v)[NV], double (&out)[N
 __device__ __forceinline__ void load_G(const double *H, double G[9], int &e) {
   __shared__ double Gs[9];
   __shared__ int es;
-  if (threadIdx.x == 0) {
+  if (static_cast<int>(threadIdx.x) == lead_thread()) {
     double g[9];
     es = adjugate_scaled(H, g);
 #pragma unroll
@@ -397,17 +458,18 @@ constexpr int kSums = 10;
 
 // The pixels [first, last) of patch b; Hb: its 9 entries of H (global or LDS).
 // PART = false: the whole patch in one workgroup, which writes the loss
-// (kLoss, kLossGrad; thread 0), the warped image (kStore), and dL/dH to gHout
-// (kGrad, kGradStored, kLossGrad; thread 0, 9 doubles). PART = true: a part of
+// (kLoss, kLossGrad), the warped image (kStore), and dL/dH to gHout (kGrad,
+// kGradStored, kLossGrad; 9 doubles). PART = true: a part of
 // the patch (first a multiple of NT kUnroll, last too or the patch's end); the
-// workgroup's kSums sums go to part (those its MODE computes; thread 0), to be
-// added over the patch's parts by a later kernel.
+// workgroup's kSums sums go to part (those its MODE computes), to be added over
+// the patch's parts by a later kernel. Thread lead_thread() writes. Returns the
+// exponent e of G = 2^-e adj(H).
 // The gradient of the loss through q = G p, position (q0, q1) / q2: with
 // g = dL/dI_w at a pixel (gl sign(r) for the L1 loss, gl a per-patch
 // constant), (a0, a1) = g iq grad I there and iq = 1/q2,
 // dL/dG row 1 += a0 p, row 2 += a1 p, row 3 += -(a0 sx + a1 sy) p.
 template <int MODE, int NT, bool ALIGNED, bool PART = false>
-__device__ __forceinline__ void warp_block(const double *Hb, const float *__restrict__ img,
+__device__ __forceinline__ int warp_block(const double *Hb, const float *__restrict__ img,
                                            const float *__restrict__ tgt, float gl, int h, int w,
                                            int b, float *__restrict__ loss,
                                            float *__restrict__ warped, double *gHout,
@@ -567,26 +629,29 @@ __device__ __forceinline__ void warp_block(const double *Hb, const float *__rest
   if (i0 - static_cast<int>(threadIdx.x) < end) iteration(i0, std::true_type());
   __builtin_amdgcn_s_setprio(0);
   fold();
+  const int lead = lead_thread();
+  const bool is_lead = static_cast<int>(threadIdx.x) == lead;
   if (LOSS && !GRAD) {
     double s1[1] = {sd[9]}, o1[1];
-    block_sum<1, NT>(s1, o1);
-    if (PART && threadIdx.x == 0) part[kSums - 1] = o1[0];
-    if (!PART && threadIdx.x == 0) loss[b] = static_cast<float>(o1[0] / static_cast<double>(P));
+    block_sum<1, NT>(s1, o1, lead);
+    if (PART && is_lead) part[kSums - 1] = o1[0];
+    if (!PART && is_lead) loss[b] = static_cast<float>(o1[0] / static_cast<double>(P));
   }
   if (GRAD) {
     double s10[NS], o10[NS];
 #pragma unroll
     for (int k = 0; k < NS; ++k) s10[k] = sd[k];
-    block_sum<NS, NT>(s10, o10);
-    if (PART && threadIdx.x == 0) {
+    block_sum<NS, NT>(s10, o10, lead);
+    if (PART && is_lead) {
 #pragma unroll
       for (int k = 0; k < (LOSS ? NS : NS - 1); ++k) part[k] = o10[k];
     }
-    if (!PART && threadIdx.x == 0) {
+    if (!PART && is_lead) {
       if (LOSS) loss[b] = static_cast<float>(o10[9] / static_cast<double>(P));
       adjugate_backward(Hb, o10, e, gHout);
     }
   }
+  return e;
 }
 
 // Per-pixel kernels: at least 4 waves per SIMD (at most 128 VGPRs).
@@ -606,13 +671,13 @@ __global__ __launch_bounds__(NT, 4) void warp_kernel(const double *__restrict__ 
 }
 
 // ---- fused offsets -> loss / gradient (one workgroup per patch) -------------
-// ACA with the rectangle's source corners runs in thread 0 of the patch's
+// ACA with the rectangle's source corners runs in one thread of the patch's
 // workgroup into LDS, then the warp; gradients go back through ACA's reverse
-// mode in thread 0. The arithmetic is that of the separate kernels.
-// Only thread 0 reads Hs (load_G and adjugate_backward run in it), so no
+// mode in that thread. The arithmetic is that of the separate kernels.
+// Only that thread reads Hs (load_G and adjugate_backward run in it), so no
 // barrier follows; load_G's barrier then publishes G to the workgroup.
 __device__ __forceinline__ void rect_to_lds(const float *o, const RectArgs &ra, double *Hs) {
-  if (threadIdx.x == 0) {
+  if (static_cast<int>(threadIdx.x) == lead_thread()) {
     double hh[9];
     rect_h(o, ra, hh);
 #pragma unroll
@@ -645,7 +710,7 @@ __global__ __launch_bounds__(NT, 4) void photo_bwd_kernel(
   const float gl = static_cast<float>(static_cast<double>(STEP ? 1.0f : grad_loss[b]) /
                                       static_cast<double>(h * w));
   warp_block<kGrad, NT, ALIGNED>(Hs, img, tgt, gl, h, w, b, nullptr, nullptr, gHs);
-  if (threadIdx.x == 0) {
+  if (static_cast<int>(threadIdx.x) == lead_thread()) {
     double g[8];
     rect_h_vjp(off + 8 * b, ra, gHs, g);
 #pragma unroll
@@ -671,7 +736,7 @@ __global__ __launch_bounds__(NT, 4) void photo_fwd_grad_kernel(
   rect_to_lds(off + 8 * b, ra, Hs);
   const float gl = static_cast<float>(1.0 / static_cast<double>(h * w));
   warp_block<kLossGrad, NT, ALIGNED>(Hs, img, tgt, gl, h, w, b, loss, nullptr, gHs);
-  if (threadIdx.x == 0) {
+  if (static_cast<int>(threadIdx.x) == lead_thread()) {
     double g[8];
     rect_h_vjp(off + 8 * b, ra, gHs, g);
 #pragma unroll
@@ -781,68 +846,96 @@ __global__ __launch_bounds__(64) void part_finish_kernel(
   }
 }
 
+// A patch between two refinement steps: its offsets, their H and the exponent
+// of 2^-e adj(H), kept so that the next step does not compute them again.
+struct RefineState {
+  double H[9];
+  float off[8];
+  int e, pad;
+};
+static_assert(sizeof(RefineState) % 16 == 0, "states are carved from a 16-byte aligned workspace");
+
+// Offsets after a step at state st with the summed parts of its gradient pass:
+// off - step * gradient.
+__device__ __forceinline__ void refine_step(const RefineState &st, const double *sum,
+                                            const RectArgs &ra, float step, float o[8]) {
+  double gH[9], g[8];
+  adjugate_backward(st.H, sum, st.e, gH);
+  rect_h_vjp(st.off, ra, gH, g);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) o[i] = st.off[i] - step * static_cast<float>(g[i]);
+}
+
 // One refinement step (LOSS = false) or the loss after the last one, over
-// parts. Its prologue finishes the step before: with prev (that step's parts;
-// NULL before the first step) every workgroup of a patch adds them, takes the
-// gradient at off_in and steps, off = off_in - step * gradient; the part 0
-// workgroup stores it in off_out. Offsets and parts alternate between two
-// buffers, since the other workgroups of a patch may still be reading.
+// parts. Its prologue finishes the step before: with prev (that step's state
+// and parts; NULL before the first step, which starts from off_in) every
+// workgroup of a patch adds the parts and steps; the part 0 workgroup stores
+// the new state in cur and, after the last step, the offsets in off_out. States
+// and parts alternate between two buffers, since the other workgroups of a
+// patch may still be reading the ones before.
 template <bool LOSS, bool ALIGNED>
 __global__ __launch_bounds__(kPartThreads, 4) void refine_part_kernel(
-    PartShape ps, const float *__restrict__ off_in, const double *__restrict__ prev,
-    const float *__restrict__ img, const float *__restrict__ tgt, int h, int w, RectArgs ra,
-    float step, float *__restrict__ off_out, double *__restrict__ part) {
+    PartShape ps, const float *__restrict__ off_in, const RefineState *__restrict__ prev,
+    const double *__restrict__ prev_part, const float *__restrict__ img,
+    const float *__restrict__ tgt, int h, int w, RectArgs ra, float step,
+    RefineState *__restrict__ cur, float *__restrict__ off_out, double *__restrict__ part) {
   __shared__ double Hs[9];
   int b, s, first, last;
   part_range(ps, h * w, b, s, first, last);
-  if (threadIdx.x < 64) {
+  const int lead = lead_thread();
+  const bool is_lead = static_cast<int>(threadIdx.x) == lead;
+  if (static_cast<int>(threadIdx.x) / 64 == lead / 64) {
+    RefineState st;
     double sum[kSums];
-    if (prev) sum_parts(prev + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
-    if (threadIdx.x == 0) {
+    if (prev) {
+      if (is_lead) st = prev[b];   // issued ahead of the parts' loads
+      sum_parts(prev_part + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
+    }
+    if (is_lead) {
       float o[8];
+      if (prev)
+        refine_step(st, sum, ra, step, o);
+      else
 #pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = off_in[8 * b + i];
-      if (prev) {
-        double Hd[9], gH[9], g[8];
-        rect_h(o, ra, Hd);
-        grad_from_sums(Hd, sum, gH);
-        rect_h_vjp(o, ra, gH, g);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) o[i] = o[i] - step * static_cast<float>(g[i]);
-      }
-      if (s == 0 && off_out)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) off_out[8 * b + i] = o[i];
+        for (int i = 0; i < 8; ++i) o[i] = off_in[8 * b + i];
       double hh[9];
       rect_h(o, ra, hh);
 #pragma unroll
       for (int i = 0; i < 9; ++i) Hs[i] = hh[i];
+      if (s == 0) {
+        if (!LOSS) {
+#pragma unroll
+          for (int i = 0; i < 9; ++i) cur[b].H[i] = hh[i];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) cur[b].off[i] = o[i];
+        } else if (prev) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) off_out[8 * b + i] = o[i];
+        }
+      }
     }
   }
   const float gl = static_cast<float>(1.0 / static_cast<double>(h * w));
-  warp_block<LOSS ? kLoss : kGrad, kPartThreads, ALIGNED, true>(
+  const int e = warp_block<LOSS ? kLoss : kGrad, kPartThreads, ALIGNED, true>(
       Hs, img, tgt, gl, h, w, b, nullptr, nullptr, nullptr, first, last,
       part + (static_cast<int64_t>(b) * ps.S + s) * kSums);
+  if (!LOSS && s == 0 && is_lead) cur[b].e = e;
 }
 
-// The last step of a refinement without a loss pass: off = off_in - step *
-// gradient, one wave per patch.
+// The last step of a refinement without a loss pass, one wave per patch.
 __global__ __launch_bounds__(64) void refine_last_kernel(PartShape ps,
-                                                         const float *__restrict__ off_in,
-                                                         const double *__restrict__ prev,
+                                                         const RefineState *__restrict__ prev,
+                                                         const double *__restrict__ prev_part,
                                                          RectArgs ra, float step,
                                                          float *__restrict__ off_out) {
   const int b = blockIdx.x;
   double sum[kSums];
-  sum_parts(prev + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
+  sum_parts(prev_part + static_cast<int64_t>(b) * ps.S * kSums, ps.S, sum);
   if (threadIdx.x != 0) return;
-  double Hd[9], gH[9], g[8];
-  rect_h(off_in + 8 * b, ra, Hd);
-  grad_from_sums(Hd, sum, gH);
-  rect_h_vjp(off_in + 8 * b, ra, gH, g);
+  float o[8];
+  refine_step(prev[b], sum, ra, step, o);
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    off_out[8 * b + i] = off_in[8 * b + i] - step * static_cast<float>(g[i]);
+  for (int i = 0; i < 8; ++i) off_out[8 * b + i] = o[i];
 }
 
 // out[b, k] = grad_loss[b] * grad_unit[b, k] (8 per patch).
@@ -861,7 +954,7 @@ __global__ void l1_fwd_kernel(const float *__restrict__ warped, const float *__r
   for (int64_t i = threadIdx.x; i < P; i += kDiffThreads)
     acc[0] += fabs(static_cast<double>(warped[b * P + i]) - static_cast<double>(tgt[b * P + i]));
   double s[1];
-  block_sum<1, kDiffThreads>(acc, s);
+  block_sum<1, kDiffThreads>(acc, s, 0);
   if (threadIdx.x == 0) loss[b] = static_cast<float>(s[0] / static_cast<double>(P));
 }
 
@@ -961,15 +1054,25 @@ struct RefineArgs {
   float *off, *loss;
 };
 
+// The rectangle with upper-left (x0, y0), width w and aspect ratio r = width /
+// height.
+static RectArgs rect_args(double x0, double y0, double w, double r) {
+  RectArgs ra;
+  ra.x0 = x0;
+  ra.y0 = y0;
+  ra.x1 = x0 + w;
+  ra.y1 = y0 + w / r;
+  ra.a = ra.x1 - ra.x0;
+  ra.b = ra.y1 - ra.y0;
+  ra.f = ra.a * ra.b;
+  return ra;
+}
+
 // The patch rectangle as hg_aca_rect_fwd receives it from a caller that
 // passes w - 1 and (w - 1) / (h - 1) as floats.
 static RectArgs patch_rect(int h, int w) {
-  RectArgs ra;
-  ra.x0 = 0.0;
-  ra.y0 = 0.0;
-  ra.w = static_cast<double>(static_cast<float>(w - 1));
-  ra.r = static_cast<double>(static_cast<float>(double(w - 1) / double(h - 1)));
-  return ra;
+  return rect_args(0.0, 0.0, static_cast<float>(w - 1),
+                   static_cast<float>(double(w - 1) / double(h - 1)));
 }
 
 // Threads per patch workgroup: enough for about WAVES waves in flight over the
@@ -1007,24 +1110,25 @@ static void with_shape(int B, int w, F &&f) {
   go(std::integral_constant<int, 256>());
 }
 
-// Parts per patch: as many as give about kPartGroups workgroups over the batch,
-// each at least one whole iteration. Cutting pays from 8 iterations a patch
-// on, and up to kPartMaxBatch patches: below 8 the second launch costs more
-// than the parts save (16 patches of 64 x 64, forward: 4.9 us whole, 6.5 us
-// cut), and with more patches the whole form fills the chip (128 x 128,
-// forward + backward in one pass: 128 patches 11.6 us whole, 11.3 us cut; 192
-// patches 12.4 and 12.5 us; 64 patches 11.3 and 8.9 us; 24 patches of
-// 211 x 317 38.4 and 12.9 us). Fewer workgroups leave compute units idle, more
-// repeat the serial prologue (24 of 211 x 317: 13.8, 13.0, 12.9 and 13.1 us for
-// 256, 512, 768 and 1024; 64 of 256 x 256: 18.3, 14.9, 14.9 and 15.8 us).
-constexpr int kPartGroups = 768;
+// Parts per patch: as many as give about 512 workgroups over the batch, or 768
+// where each of 512 would have more than 8 iterations; each part at least one
+// whole iteration. Cutting pays from 8 iterations a patch on, and up to
+// kPartMaxBatch patches: below 8 the second launch costs more than the parts
+// save (16 patches of 64 x 64, forward: 4.7 us whole, 6.6 us cut), and with
+// more patches the whole form fills the chip (128 x 128, loss and gradient: 128
+// patches 11.1 us whole, 10.3 us cut; 192 patches 11.4 and 12.4 us; 64 patches
+// 11.1 and 8.5 us; 24 patches of 211 x 317 38.1 and 12.7 us). Fewer workgroups
+// leave compute units idle, more repeat the serial prologue (six steps on 64
+// patches of 128 x 128: 53 us with 512 workgroups, 61 us with 1024; on 128 of
+// 256 x 256: 146 us with 512, 134 us with 768, 144 us with 1024).
 constexpr int kPartMaxBatch = 128;
 constexpr int kPartMinIters = 8;
 static PartShape split_parts(int B, int h, int w) {
   PartShape ps = {B, 1, 0};
   const int iters = (h * w + kPartPixels - 1) / kPartPixels;
   if (B < 1 || B > kPartMaxBatch || iters < kPartMinIters) return ps;
-  const int want = std::min(iters, (kPartGroups + B - 1) / B);
+  const int groups = static_cast<int64_t>(iters) * B > 8 * 512 ? 768 : 512;
+  const int want = std::min(iters, (groups + B - 1) / B);
   ps.per = (iters + want - 1) / want;
   ps.S = (iters + ps.per - 1) / ps.per;
   return ps;
@@ -1034,9 +1138,9 @@ static size_t part_bytes(const PartShape &ps) {
   return sizeof(double) * kSums * static_cast<size_t>(ps.B) * ps.S;
 }
 
-// Workspace of hg_refine_ws: two sets of parts and two of offsets.
+// Workspace of hg_refine_ws: two sets of parts and two of states.
 static size_t refine_bytes(const PartShape &ps) {
-  return 2 * (part_bytes(ps) + 8 * sizeof(float) * static_cast<size_t>(ps.B));
+  return 2 * (part_bytes(ps) + sizeof(RefineState) * static_cast<size_t>(ps.B));
 }
 
 // The split shape to use with workspace ws (NULL: one workgroup per patch).
@@ -1083,35 +1187,35 @@ static int launch_refine_parts(const RefineArgs &a, const PartShape &ps, void *w
                                hipStream_t s) {
   const RectArgs ra = patch_rect(a.h, a.w);
   double *part[2];
-  float *off[2];
-  part[0] = static_cast<double *>(ws);
+  RefineState *st[2];
+  st[0] = static_cast<RefineState *>(ws);
+  st[1] = st[0] + ps.B;
+  part[0] = reinterpret_cast<double *>(st[1] + ps.B);
   part[1] = part[0] + part_bytes(ps) / sizeof(double);
-  off[0] = reinterpret_cast<float *>(part[1] + part_bytes(ps) / sizeof(double));
-  off[1] = off[0] + 8 * static_cast<size_t>(ps.B);
-  const float *from = a.off;
-  const double *prev = nullptr;
+  const RefineState *prev = nullptr;
+  const double *prev_part = nullptr;
   for (int it = 0; it < a.iters; ++it) {
     with_aligned(a.w, [&](auto al) {
       hipLaunchKernelGGL((refine_part_kernel<false, decltype(al)::value>), dim3(ps.B * ps.S),
-                         dim3(kPartThreads), 0, s, ps, from, prev, a.img, a.tgt, a.h, a.w, ra,
-                         a.step, off[it & 1], part[it & 1]);
+                         dim3(kPartThreads), 0, s, ps, a.off, prev, prev_part, a.img, a.tgt, a.h,
+                         a.w, ra, a.step, st[it & 1], nullptr, part[it & 1]);
     });
-    if (int st = launched("refine_part_kernel")) return st;
-    from = off[it & 1];
-    prev = part[it & 1];
+    if (int r = launched("refine_part_kernel")) return r;
+    prev = st[it & 1];
+    prev_part = part[it & 1];
   }
   if (!a.loss) {
     if (a.iters == 0) return HG_OK;
-    hipLaunchKernelGGL(refine_last_kernel, dim3(ps.B), dim3(64), 0, s, ps, from, prev, ra, a.step,
-                       a.off);
+    hipLaunchKernelGGL(refine_last_kernel, dim3(ps.B), dim3(64), 0, s, ps, prev, prev_part, ra,
+                       a.step, a.off);
     return launched("refine_last_kernel");
   }
   with_aligned(a.w, [&](auto al) {
     hipLaunchKernelGGL((refine_part_kernel<true, decltype(al)::value>), dim3(ps.B * ps.S),
-                       dim3(kPartThreads), 0, s, ps, from, prev, a.img, a.tgt, a.h, a.w, ra, a.step,
-                       a.iters ? a.off : nullptr, part[a.iters & 1]);
+                       dim3(kPartThreads), 0, s, ps, a.off, prev, prev_part, a.img, a.tgt, a.h, a.w,
+                       ra, a.step, nullptr, a.off, part[a.iters & 1]);
   });
-  if (int st = launched("refine_part_kernel<loss>")) return st;
+  if (int r = launched("refine_part_kernel<loss>")) return r;
   hipLaunchKernelGGL((part_finish_kernel<kLoss, true>), dim3(ps.B), dim3(64), 0, s, ps, nullptr,
                      nullptr, a.h * a.w, ra, part[a.iters & 1], a.loss, nullptr, nullptr);
   return launched("part_finish_kernel<loss>");
@@ -1181,8 +1285,7 @@ extern "C" int hg_aca_rect_fwd(const float *offsets, int32_t B, float x0, float 
   if (B == 0) return HG_OK;
   HG_REQUIRE(offsets && H, "hg_aca_rect_fwd: NULL pointer");
   HG_REQUIRE(std::isfinite(x0) && std::isfinite(y0), "hg_aca_rect_fwd: non-finite origin");
-  const RectArgs ra = {static_cast<double>(x0), static_cast<double>(y0), static_cast<double>(w),
-                       static_cast<double>(r)};
+  const RectArgs ra = rect_args(x0, y0, w, r);
   hipLaunchKernelGGL(rect_fwd_kernel, dim3((B + 255) / 256), dim3(256), 0, as_stream(stream),
                      offsets, B, ra, H);
   return launched("rect_fwd_kernel");
@@ -1195,8 +1298,7 @@ extern "C" int hg_aca_rect_bwd(const float *offsets, const double *grad_H, int32
   if (B == 0) return HG_OK;
   HG_REQUIRE(offsets && grad_H && grad_offsets, "hg_aca_rect_bwd: NULL pointer");
   HG_REQUIRE(std::isfinite(x0) && std::isfinite(y0), "hg_aca_rect_bwd: non-finite origin");
-  const RectArgs ra = {static_cast<double>(x0), static_cast<double>(y0), static_cast<double>(w),
-                       static_cast<double>(r)};
+  const RectArgs ra = rect_args(x0, y0, w, r);
   hipLaunchKernelGGL(rect_bwd_kernel, dim3((B + 255) / 256), dim3(256), 0, as_stream(stream),
                      offsets, grad_H, B, ra, grad_offsets);
   return launched("rect_bwd_kernel");
