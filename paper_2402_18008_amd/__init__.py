@@ -15,6 +15,13 @@ import torch
 from . import _abi
 from ._abi import HG_ACA, HG_SKS, HomogError, Tuning  # noqa: F401
 
+try:
+    # the native call path (csrc/binding.cpp): each call below is offered to it first,
+    # and it answers None for what it leaves to the Python code that follows
+    from . import _native
+except ImportError:   # not built yet (the build imports this package)
+    _native = None
+
 __all__ = ["hg_solve4", "solve4", "HomogError", "HG_ACA", "HG_SKS"]
 
 
@@ -44,6 +51,9 @@ def hg_solve4(src, dst, method=HG_ACA, H=None, flags=None, stream=None):
     yN xP yP xQ yQ sharing one plane stride). Returns (H (9, n) float32 planes
     h11..h33, flags (n,) uint8). ``method`` is HG_ACA or HG_SKS (or "aca",
     "sks")."""
+    r = _native and _native.solve4(src, dst, method, H, flags, stream)
+    if r is not None:
+        return r
     if isinstance(method, str):
         method = {"aca": HG_ACA, "sks": HG_SKS}[method.lower()]
     ld = _planes(src, "src", 8)
@@ -71,6 +81,9 @@ def hg_solve_sk(obj, dst, H=None, flags=None, stream=None):
     planes). Returns (Hbar (9, n) planes, flags (n,), H_S1 (3, 3) float64
     numpy array) with the object-to-image homography Hbar H_S1 up to scale."""
     import numpy as np
+    r = _native and _native.solve_sk(tuple(map(float, obj)), dst, H, flags, stream)
+    if r is not None:
+        return r[0], r[1], np.array(r[2], dtype=np.float64).reshape(3, 3)
     o = (C.c_double * 8)(*[float(v) for v in obj])
     frame = (C.c_double * 9)()
     ld = _planes(dst, "dst", 8)
@@ -91,6 +104,9 @@ def hg_solve3_affine(src, dst, A=None, flags=None, stream=None):
     """Affine map through three correspondences for every column of
     ``src``/``dst`` ((6, n) float32 planes xM yM xN yN xP yP sharing one plane
     stride). Returns (A (6, n) planes a11 a12 a13 a21 a22 a23, flags (n,))."""
+    r = _native and _native.solve3_affine(src, dst, A, flags, stream)
+    if r is not None:
+        return r
     ld = _planes(src, "src", 6)
     if _planes(dst, "dst", 6) != ld:
         raise ValueError("src and dst must share the plane stride")
@@ -165,6 +181,10 @@ def _ws(nbytes, device, ws):
 
 
 def _ransac(name, corr, n_hyp, thresh, seed, want_counts, ws, stream):
+    r = _native and _native.ransac(name == "hg_ransac_plain", corr, int(n_hyp), float(thresh),
+                                   int(seed), want_counts, ws, stream)
+    if r is not None:
+        return r
     ld, n = _corr_planes(corr)
     dev = corr.device
     ws = _ws(hg_ransac_ws_bytes(n, n_hyp), dev, ws)
@@ -268,6 +288,9 @@ def hg_refit_ho(corr, off, mask=None, H=None, n_used=None, flags=None, stream=No
     copy of off for the checks (else off is copied back, which waits for the
     stream). Returns (H (n_pairs, 9) float32, n_used (n_pairs,) int32, flags
     (n_pairs,) uint8)."""
+    r = _native and _native.refit_ho(corr, off, mask, H, n_used, flags, stream, off_host)
+    if r is not None:
+        return r
     ld, total = _corr_planes(corr)
     _check_off(off, total, 0, off_host=off_host)
     n_pairs = off.numel() - 1
@@ -423,6 +446,9 @@ def _c(t, name, dtype=torch.float32):
 def hg_aca_rect_fwd(offsets, x0, y0, w, r, stream=None):
     """H (B, 9) float64 from offsets (B, 4, 2) float32 [TL, TR, BR, BL] by
     ACA with the source corners at the rectangle's."""
+    out = _native and _native.aca_rect_fwd(offsets, x0, y0, w, r, stream)
+    if out is not None:
+        return out
     _c(offsets, "offsets")
     B = offsets.shape[0]
     H = torch.empty((B, 9), dtype=torch.float64, device=offsets.device)
@@ -432,6 +458,9 @@ def hg_aca_rect_fwd(offsets, x0, y0, w, r, stream=None):
 
 
 def hg_aca_rect_bwd(offsets, grad_H, x0, y0, w, r, stream=None):
+    out = _native and _native.aca_rect_bwd(offsets, grad_H, x0, y0, w, r, stream)
+    if out is not None:
+        return out
     _c(offsets, "offsets")
     _c(grad_H, "grad_H", torch.float64)
     B = offsets.shape[0]
@@ -451,6 +480,9 @@ def _quad_rows(t, name):
 def hg_aca_fwd(src, dst, stream=None):
     """H (B, 9) float64 at ACA's own scale from general quadrilaterals src,
     dst ((B, 8) or (B, 4, 2) float32, points M N P Q)."""
+    r = _native and _native.aca_fwd(src, dst, stream)
+    if r is not None:
+        return r
     B = _quad_rows(src, "src")
     if _quad_rows(dst, "dst") != B:
         raise ValueError("src and dst must have the same batch size")
@@ -461,6 +493,9 @@ def hg_aca_fwd(src, dst, stream=None):
 
 def hg_aca_bwd(src, dst, grad_H, want_src=True, want_dst=True, stream=None):
     """(grad_src, grad_dst), each shaped like src (or None when not wanted)."""
+    r = _native and _native.aca_bwd(src, dst, grad_H, want_src, want_dst, stream)
+    if r is not None:
+        return r
     B = _quad_rows(src, "src")
     _quad_rows(dst, "dst")
     _c(grad_H, "grad_H", torch.float64)
@@ -517,6 +552,9 @@ def _part_ws(B, h, w, device, stream):
 
 
 def hg_warp_l1_fwd(H, img, tgt, stream=None):
+    r = _native and _native.warp_l1_fwd(H, img, tgt, stream)
+    if r is not None:
+        return r
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
     _c(H, "H", torch.float64)
@@ -528,6 +566,9 @@ def hg_warp_l1_fwd(H, img, tgt, stream=None):
 
 
 def hg_warp_l1_bwd(H, img, tgt, grad_loss, stream=None):
+    r = _native and _native.warp_l1_bwd(H, img, tgt, grad_loss, stream)
+    if r is not None:
+        return r
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
     _c(H, "H", torch.float64)
@@ -610,6 +651,9 @@ class WarpL1(torch.autograd.Function):
 
 def hg_photometric_fwd(offsets, img, tgt, stream=None):
     """Fused offsets (B, 4, 2) -> per-patch loss (B,) (ACA + warp + L1)."""
+    r = _native and _native.photometric_fwd(offsets, img, tgt, stream)
+    if r is not None:
+        return r
     _c(offsets, "offsets")
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
@@ -622,6 +666,9 @@ def hg_photometric_fwd(offsets, img, tgt, stream=None):
 
 def hg_photometric_bwd(offsets, img, tgt, grad_loss, stream=None):
     """Fused gradient: grad_loss[b] * dloss_b/d offsets_b, (B, 4, 2) float32."""
+    r = _native and _native.photometric_bwd(offsets, img, tgt, grad_loss, stream)
+    if r is not None:
+        return r
     _c(offsets, "offsets")
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
@@ -636,6 +683,9 @@ def hg_photometric_bwd(offsets, img, tgt, grad_loss, stream=None):
 def hg_photometric_fwd_grad(offsets, img, tgt, stream=None):
     """Loss and its gradient in one pass: (loss (B,), grad_unit (B, 4, 2)) with
     grad_unit[b] = dloss_b/d offsets_b."""
+    r = _native and _native.photometric_fwd_grad(offsets, img, tgt, stream)
+    if r is not None:
+        return r
     _c(offsets, "offsets")
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
@@ -649,6 +699,9 @@ def hg_photometric_fwd_grad(offsets, img, tgt, stream=None):
 
 def hg_scale_grad(grad_unit, grad_loss, stream=None):
     """grad_loss[b] * grad_unit[b] for (B, 4, 2) grad_unit, (B,) grad_loss."""
+    r = _native and _native.scale_grad(grad_unit, grad_loss, stream)
+    if r is not None:
+        return r
     _c(grad_unit, "grad_unit")
     _c(grad_loss, "grad_loss")
     B = grad_unit.shape[0]

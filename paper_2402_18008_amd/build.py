@@ -1,4 +1,5 @@
-"""Build libhomog.so (HIP, gfx950) next to this file.
+"""Build libhomog.so (HIP, gfx950) and the binding's native call path
+(_native.so, host code against torch's headers) next to this file.
 
 Usage: python -m paper_2402_18008_amd.build   (or build() from Python)
 """
@@ -8,11 +9,13 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhomog.so")
+NATIVE = os.path.join(HERE, "_native.so")
 
 SOURCES = ["status.hip", "solve.hip", "ransac.hip", "diff.hip", "refit.hip", "stream.hip"]
 
@@ -37,17 +40,43 @@ def hipcc():
     raise RuntimeError("hipcc not found")
 
 
-def build(verbose=False):
-    srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", tmp, *srcs]
+def _run(cmd, what, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)
-        raise RuntimeError("hipcc failed building libhomog.so")
+        raise RuntimeError(f"{cmd[0]} failed building {what}")
+
+
+def build_native(verbose=False):
+    """_native.so: the host compiler, torch's headers and libraries; it finds
+    libhomog.so beside itself."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    inc = [os.path.join(ROOT, "include"), os.path.join(root, "include"),
+           os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
+           sysconfig.get_paths()["include"]]
+    tmp = NATIVE + ".tmp"
+    cmd = [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *(f for i in inc for f in ("-isystem", i)), "-o", tmp,
+           os.path.join(CSRC, "binding.cpp"), LIB, "-L", os.path.join(root, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-Wl,-rpath,$ORIGIN"]
+    _run(cmd, "_native.so", verbose)
+    os.replace(tmp, NATIVE)
+    return NATIVE
+
+
+def build(verbose=False):
+    srcs = [os.path.join(CSRC, s) for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
+    tmp = LIB + ".tmp"
+    cmd = [hipcc(), *HIPCC_FLAGS, "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", tmp, "-Wl,-soname,libhomog.so", *srcs]
+    _run(cmd, "libhomog.so", verbose)
     os.replace(tmp, LIB)
+    build_native(verbose)
     return LIB
 
 
