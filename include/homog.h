@@ -193,8 +193,9 @@ int hg_ransac_noalloc(const float *corr, int32_t n_pts, int64_t ld, int32_t n_hy
  *   tune        launch shape, NULL = the cached autotuned or default choice.
  *   ws          >= hg_ransac_batched_ws_bytes(n_pairs, n_hyp) bytes.       */
 typedef struct {
-  int32_t pts_per_lane;    /* points held in registers per lane: 8 or 16    */
-  int32_t hyps_per_block;  /* hypotheses per work item: 16, 32 or 64         */
+  int32_t pts_per_lane;    /* 8 or 16: points a lane of a wave counts between
+                              checks for open decisions (two of its columns) */
+  int32_t hyps_per_block;  /* hypotheses per work item: 32 or 64 (16 = 32)   */
   int32_t blocks_per_cu;   /* persistent blocks per compute unit: 1..8       */
   int32_t reserved;        /* 0                                              */
 } hg_ransac_tuning;
@@ -252,9 +253,8 @@ int hg_ransac_adaptive(const float *corr, int64_t ld, const int64_t *off, int32_
 int hg_refit_ho(const float *corr, int64_t ld, const int64_t *off, int32_t n_pairs,
                 const uint8_t *mask, float *H, int32_t *n_used, uint8_t *flags, void *stream);
 
-/* Times the tunings {8, 16} points per lane x {16, 32, 64} hypotheses per
- * block x {1, 2, 4, 5, 6} blocks per compute unit on the given problem (7 and
- * 8 blocks per unit do not fit in the registers at once); allocates temporary
+/* Times the tunings {8, 16} points per lane x {32, 64} hypotheses per block x
+ * {1, 2, 4, 5, 6} blocks per compute unit on the given problem; allocates temporary
  * outputs and synchronises the stream. Stores the fastest in *out and in the
  * process-wide cache used when tune == NULL; also written to the JSON file
  * named by HG_AUTOTUNE_CACHE if that variable is set. off_host mirrors off. */

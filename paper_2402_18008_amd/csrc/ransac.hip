@@ -1,20 +1,27 @@
 // RANSAC hypothesise-and-verify on the GPU.
 //
-// Work item = (pair, block of HB hypotheses). A workgroup (256 threads; 512
-// for the fused single pair) solves its HB hypotheses (one per thread) into
-// LDS, then scores them against the pair's points: each lane holds P correspondences in registers, every lane
-// reads the hypothesis from LDS, the inlier test runs per (hypothesis, point)
-// and counts come from a wavefront ballot + popcount. The argmax is over a
-// packed (count, ~index) key.
+// Two forms of scoring, both of which decide a point in float only where a bound
+// on the rounding error proves the decision and leave the rest to a float64
+// recount, so that every count is the float64 test's:
+//  * vector form (single pair): each lane holds P correspondences in registers,
+//    every lane reads the hypothesis from LDS, the inlier test runs per
+//    (hypothesis, point) and counts come from a wavefront ballot + popcount.
+//    Its work is split into blocks of few hypotheses, which fills the chip from
+//    one pair;
+//  * tile form (many pairs): tiles of 32 hypotheses x 32 points on the matrix
+//    cores, counts summed in the lanes.
+// The argmax is over a packed (count, ~index) key.
 //
-// Forms:
-//  * fused single pair: grid = hypothesis blocks, each writing its best key;
-//    a second kernel reduces them and writes the mask;
+// Launches:
+//  * fused single pair: grid = hypothesis blocks, each workgroup (512 threads)
+//    solving and scoring its hypotheses and writing its best key; a second
+//    kernel reduces them and writes the mask;
 //  * plain single pair: solve all -> H buffer, score, argmax, mask kernels;
-//  * batched persistent: CUs x blocks_per_cu workgroups drain an atomic queue
-//    of items ordered by pair size (largest first); each item atomicMax-es its
-//    key into the pair's; a finish kernel (one workgroup per pair) then
-//    recomputes each winner and writes the outputs and masks;
+//  * batched persistent: CUs x blocks_per_cu workgroups (256 threads) drain an
+//    atomic queue of items (pair, block of hypotheses) ordered by pair size
+//    (largest first); each item atomicMax-es its key into the pair's; a finish
+//    kernel (one workgroup per pair) then recomputes each winner and writes the
+//    outputs and masks;
 //  * adaptive termination: items are rounds of 64 hypotheses; each writes its
 //    round key into a write-once slot and may advance an advisory prefix that
 //    lets later rounds be skipped; the finish kernel applies the stopping rule
@@ -70,6 +77,7 @@ struct RansacArgs {
   struct PairState *pst;
   unsigned long long *rkey;
   int32_t *iorder;         // adaptive: queue position -> pair * n_hb + round, or NULL
+  struct Extent *extent;   // many pairs: centre and reach of each pair's points
   int32_t *n_eval;
   double one_minus_conf;
 };
@@ -89,6 +97,13 @@ struct PairState {
 
 // Round key slot not yet published (no real key has all bits set).
 constexpr unsigned long long kUnpublished = ~0ull;
+
+// Where a pair's points lie (those with four finite coordinates; the others are
+// outliers to every hypothesis): x1 and y1 within r1 of c1, and x2 / tau and
+// y2 / tau, in the float arithmetic of the scoring, within r2 of k2.
+struct Extent {
+  float c1[2], k2[2], r1[2], r2[2];
+};
 
 // Hypotheses per round under adaptive termination (one work item).
 constexpr int kRoundHyps = 64;
@@ -243,18 +258,12 @@ __device__ void fix_counts(const RansacArgs &a, int64_t base, uint32_t n, const 
 // float64 recount after the loop (fix_counts). The error bound's magnitudes
 // are the wave's maxima over its points, and its coefficients are computed
 // once per chunk, lane h for hypothesis h.
-// Under adaptive termination `stop` points at the pair's stopping hint and
-// `hb` is this item's round: every 8 hypotheses the wave compares hb with the
-// value it loaded at the previous check (the load's latency overlaps the 8
-// hypotheses) and gives up a round that is no longer needed (returns false).
-// Rounds at or past the hint are never needed, so an abandoned round changes
-// no result.
 template <int P, bool TAIL, int NW>
-__device__ __forceinline__ bool score_chunk(const RansacArgs &a, const float *X1, const float *Y1,
+__device__ __forceinline__ void score_chunk(const RansacArgs &a, const float *X1, const float *Y1,
                                             const float *X2, const float *Y2, uint32_t c0,
                                             uint32_t n, const float (*Hs)[9],
                                             uint64_t vmask, int nh, uint32_t *cnt,
-                                            FixList *fx, const uint32_t *stop, uint32_t hb) {
+                                            FixList *fx) {
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   float x1[P], y1[P], x2[P], y2[P];
@@ -281,13 +290,7 @@ __device__ __forceinline__ bool score_chunk(const RansacArgs &a, const float *X1
   // lane h: error-bound coefficients of hypothesis h over this wave's points
   float k1v = 0.0f, k0v = 0.0f;
   if (lane < nh) error_bound(Hs[lane], m1, m2, m3, m4, k1v, k0v);
-  uint32_t stop_seen =
-      stop ? __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
   for (int h = 0; h < nh; ++h) {
-    if (stop && (h & 7) == 7) {
-      if (hb >= stop_seen) return false;
-      stop_seen = __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     if (!((vmask >> h) & 1ull)) continue;
     // H read from LDS by every lane (one address: a broadcast) and used from
     // vector registers; scalar copies would cost a readfirstlane per entry and
@@ -334,40 +337,30 @@ __device__ __forceinline__ bool score_chunk(const RansacArgs &a, const float *X1
     }
     if (lane == 0 && c) atomicAdd(&cnt[h], c);
   }
-  return true;
 }
 
-// Full chunks of P points per lane, then (P = 16) chunks of 8, then one
-// masked tail chunk of just enough 64-point rows per wave (1 to 8), so that a
+// Full chunks of P points per lane, then one masked tail chunk of just enough 64-point rows per wave (1 to 8), so that a
 // pair's last chunk leaves fewer than NW x 64 lane slots idle (NW: waves per
 // workgroup). Counts are integer sums over the points, so the result does not
 // depend on the chunking.
 template <int P, int NW = kWaves>
 __device__ __forceinline__ void score_hyps(const RansacArgs &a, int64_t base, uint32_t n,
                                            const float (*Hs)[9], uint64_t vmask, int nh,
-                                           uint32_t *cnt, FixList *fx,
-                                           const uint32_t *stop = nullptr,
-                                           uint32_t hb = 0u) {
+                                           uint32_t *cnt, FixList *fx) {
+  static_assert(P == 8, "the tail has at most 8 rows");
   const float *X1 = a.corr + base, *Y1 = a.corr + a.ld + base;
   const float *X2 = a.corr + 2 * a.ld + base, *Y2 = a.corr + 3 * a.ld + base;
   constexpr uint32_t kChunk = NW * 64 * P;
-  constexpr uint32_t kChunk8 = NW * 64 * 8;
   uint32_t c0 = 0;
   for (; c0 + kChunk <= n; c0 += kChunk)
-    if (!score_chunk<P, false, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx, stop, hb))
-      return;
-  if (P > 8) {
-    for (; c0 + kChunk8 <= n; c0 += kChunk8)
-      if (!score_chunk<8, false, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx, stop, hb))
-        return;
-  }
+    score_chunk<P, false, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx);
   if (c0 < n) {
-    // fewer than kChunk8 points remain: 1 .. 8 rows of 64 points per wave
+    // fewer than kChunk points remain: 1 .. 8 rows of 64 points per wave
     const uint32_t rows = (n - c0 + 63u) / 64u;
     switch ((rows + NW - 1) / NW) {
 #define HG_TAIL(R) \
   case R:          \
-    score_chunk<R, true, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx, stop, hb); \
+    score_chunk<R, true, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx); \
     break;
       HG_TAIL(1)
       HG_TAIL(2)
@@ -377,10 +370,274 @@ __device__ __forceinline__ void score_hyps(const RansacArgs &a, int64_t base, ui
       HG_TAIL(6)
       HG_TAIL(7)
       default:
-        score_chunk<8, true, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx, stop, hb);
+        score_chunk<8, true, NW>(a, X1, Y1, X2, Y2, c0, n, Hs, vmask, nh, cnt, fx);
 #undef HG_TAIL
     }
   }
+}
+
+// ---- scoring on the matrix cores (many pairs) --------------------------------
+// A wave scores tiles of 32 hypotheses x 32 points. u, v and w of a tile (the
+// rows of the scoring form times (x1, y1, 1)) come from one
+// v_mfma_f32_32x32x16_bf16 each: a float is exactly the sum of three bfloat16
+// pieces, and the six products of pieces that reach 2^-22 of a term, for x1 and
+// y1, and the three pieces of the constant fill 15 of the 16 slots of K:
+//   point       x0 x0 x1 x1 x0 x2 | 1 1    y0 y0 y1 y1 y0 y2 | 1 0
+//   hypothesis  g0 g1 g0 g1 g2 g0 | c0 c1  (the same for y)  | c2 0
+// Lane l holds slots 8 (l / 32) .. + 7 of hypothesis (operand A) or point
+// (operand B) l % 32, and gets hypothesis m = 8 (i / 4) + 4 (l / 32) + i % 4 of
+// point l % 32 in result i.
+// The rest runs in float on the results, 7 instructions per element:
+//   ru = u - x2c w, rv = v - y2c w, t = clamp(w^2 - (rv^2 + (ru^2 - 0.5)))
+// with the rows scaled by sigma so that the error bound of e = ru^2 + rv^2 - w^2
+// becomes 0.5: t = 1 proves an inlier, t = 0 an outlier, and anything between
+// leaves the point open. Sums of t and t^2 per lane count the inliers and show
+// by their difference whether a point was open (0 and 1 are their own squares),
+// so counting needs neither compares nor ballots. Every kTileBlock tiles a lane
+// whose sums differ lists its points (one column of the block) for a float64
+// recount and leaves them out.
+//
+// What bounds it: vector issue and the clock that the power limit leaves (1.95
+// GHz measured). Of gfx950's vector instructions only float add, mul, FMA (no
+// scalar operand, not all three sources in one register bank), 32-bit integer
+// add and logic issue every 2 cycles per wave, and compares, min / max and
+// conversions every 4; matrix instructions do not overlap them. Per 64
+// (hypothesis, point) pairs the vector form (score_chunk) spends 12 float
+// instructions, a compare, the minimum and the per-hypothesis overheads, 52
+// cycles of 2.4 GHz in all; here 7 float instructions and 1/16 of the three
+// MFMAs (33 cycles each), 31 - 35 cycles. For v and w, A holds hypothesis
+// (l % 32) ^ 1, so that results i of u and i ^ 1 of v and w belong together:
+// the three results start at even registers, and equal indices would put all
+// sources of the squares into one bank (35.5 against 31.4 cycles).
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Two floats rounded to nearest bfloat16 (a in the low half).
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = {static_cast<__bf16>(a), static_cast<__bf16>(b)};
+  return __builtin_bit_cast(uint32_t, v);
+}
+__device__ __forceinline__ float high_bf16(uint32_t p) {
+  return __uint_as_float(p & 0xffff0000u);
+}
+
+// Operand B of a point: this lane's coordinate c (x1 or y1); one = its
+// constants (1 1 or 1 0).
+__device__ __forceinline__ bf16x8 point_operand(float c, uint32_t one) {
+  u32x4 v;
+  v[0] = pack_bf16(c, c);
+  const float r1 = c - high_bf16(v[0]);
+  v[1] = pack_bf16(r1, r1);
+  const float r2 = r1 - high_bf16(v[1]);
+  v[2] = pack_bf16(c, r2);
+  v[3] = one;
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+// The three bfloat16 pieces of a float, as floats (their sum is exactly x).
+__device__ __forceinline__ void pieces(float x, float f[3]) {
+  f[0] = x;
+  f[1] = x - high_bf16(pack_bf16(0.0f, x));
+  f[2] = f[1] - high_bf16(pack_bf16(0.0f, f[1]));
+}
+
+// Operand A of one row, the slots of one half: g = its x1 or y1 coefficient, c =
+// its constant (rounded by pack_bf16, which leaves the pieces).
+__device__ __forceinline__ u32x4 row_operand(const float g[3], const float c[3], int half) {
+  u32x4 v;
+  v[0] = v[1] = pack_bf16(g[0], g[1]);
+  v[2] = pack_bf16(g[2], g[0]);
+  v[3] = half ? pack_bf16(c[2], 0.0f) : pack_bf16(c[0], c[1]);
+  return v;
+}
+
+// Bound on |e_computed - e| for the tile form over points with |x1 - c| <=
+// r1[0], |y1 - c| <= r1[1], |x2c| <= r2[0], |y2c| <= r2[1], rows g on centred
+// coordinates. With u = 2^-24, SU = |g0| r1[0] + |g1| r1[1] + |g2| and SV, SW
+// likewise, a row's product errs by at most 8.3 u of its magnitude sum (measured
+// over random, wide-range and cancelling operands: at most 5.4 u, 0.7 u rms; the
+// dropped products are at most 2 u of it), the rounding of g by 0.5 u, the centred
+// point and x2c by u each, so ru and rv together by S = 10.5 u (SU + SV +
+// (r2[0] + r2[1]) SW) beside their own rounding. A wrong decision needs the true
+// or the computed d = ru^2 + rv^2 at or below w^2 <= SW^2, hence |ru|, |rv| <=
+// SW (1 + small), and then the errors of the residuals (2 SW S + S^2), of w
+// (2 SW 8.6 u SW), of 1/tau (u SW^2) and of the squares, sums and the last FMA
+// (5 u SW^2) stay below
+//   SW (27 u SW + 2.25 S) + 2 S^2,
+// which leaves a tenth for sigma's rounding and the float64 test's own error.
+// False: the magnitudes leave the range where that holds (the hypothesis is
+// then counted in float64 throughout).
+__device__ __forceinline__ bool tile_bound(const double *g, const Extent &x, float &bound) {
+  constexpr float u = 5.9604645e-08f;   // 2^-24
+  float s[3];
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    s[r] = fmaf(fabsf(static_cast<float>(g[3 * r])), x.r1[0],
+                fmaf(fabsf(static_cast<float>(g[3 * r + 1])), x.r1[1],
+                     fabsf(static_cast<float>(g[3 * r + 2]))));
+  const float sw = s[2];
+  const float mag = fmaf(x.r2[0] + x.r2[1], sw, s[0] + s[1]);
+  const float S = (10.5f * u) * mag;
+  bound = fmaf(sw, fmaf(27.0f * u, sw, 2.25f * S), fmaf(2.0f * S, S, 1.0e-35f));
+  return mag + sw < 1.0e18f && sw > 1.0e-18f;
+}
+
+// A hypothesis for the tile form: its float H, solver flags, and the rows g that
+// go into operand A (centred, scaled by 1/tau and sigma). full: without a bound, to be
+// counted in float64 throughout. An invalid, missing or full one gets u = 1024,
+// v = w = 0: no inlier and nothing open anywhere.
+__device__ __forceinline__ uint32_t tile_hypothesis(const RansacArgs &a, int64_t base, uint32_t n,
+                                                    int p, int hyp, bool live, float *h,
+                                                    double *g, bool &full) {
+  uint32_t f = kZeroH;
+  if (live)
+    f = make_hypothesis(a.corr, a.ld, base, n, a.k0, a.k1, static_cast<uint32_t>(hyp),
+                        static_cast<uint32_t>(p), h);
+  full = false;
+  if (f == 0u) {
+    // rows on coordinates about the pair's centre: halves the magnitudes, and
+    // with them the error bound and the points that stay open
+    const Extent x = a.extent[p];
+    const double it = static_cast<double>(a.inv_tau);
+#pragma unroll
+    for (int r = 2; r >= 0; --r) {
+      const double scale = r == 2 ? 1.0 : it, k = r == 2 ? 0.0 : static_cast<double>(x.k2[r]);
+      const double h0 = h[3 * r], h1 = h[3 * r + 1];
+      const double h2 = h[3 * r + 2] + (h0 * x.c1[0] + h1 * x.c1[1]);
+      g[3 * r] = r == 2 ? h0 : h0 * scale - k * g[6];
+      g[3 * r + 1] = r == 2 ? h1 : h1 * scale - k * g[7];
+      g[3 * r + 2] = r == 2 ? h2 : h2 * scale - k * g[8];
+    }
+    float bound;
+    full = !tile_bound(g, x, bound);
+    // bound sigma^2 = 0.5 (to a rounding or two of the reciprocal root)
+    const double sigma = static_cast<double>(__builtin_amdgcn_rsqf(2.0f * bound));
+#pragma unroll
+    for (int k = 0; k < 9; ++k) g[k] *= sigma;
+  }
+  if (f != 0u || full)
+#pragma unroll
+    for (int k = 0; k < 9; ++k) g[k] = k == 2 ? 1024.0 : 0.0;
+  return f;
+}
+
+// Points whose decision is open, listed by the tile loop: the first of their
+// tiles and hypothesis | column << 6 | number of tiles << 11. n counts every
+// append; the hypotheses (bit m of lost) of those past the capacity are counted
+// in float64 throughout.
+template <int CAP>
+struct OpenList {
+  uint32_t n;
+  uint32_t lost[2];
+  uint32_t e[CAP][2];
+};
+
+// The lane number, opaque to the compiler: what is computed from it stays where
+// it is used. Hoisted out of the persistent loop, such values (LDS addresses,
+// mostly) exceed the registers beside the tile loop's and cost scratch reloads
+// in every item.
+__device__ __forceinline__ uint32_t lane_here() {
+  uint32_t lane = threadIdx.x & 63u;
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
+// Score the 32 hypotheses of operands au, av, aw (numbers m0 .. m0 + 31 in the
+// item) against tiles [t0, t1) of a segment of n points, whose first tile is
+// number first_tile of the pair; adds the inliers to tot (by result and lane)
+// and lists open points. Returns false if the item is abandoned (adaptive:
+// round hb is at or past the stopping hint, checked once per block of tiles).
+template <int TB, int CAP>
+__device__ __forceinline__ bool score_tiles(const RansacArgs &a, const float *X1, const float *Y1,
+                                            const float *X2, const float *Y2, uint32_t n,
+                                            uint32_t t0, uint32_t t1, uint32_t first_tile,
+                                            uint32_t m0, bf16x8 au, bf16x8 av, bf16x8 aw,
+                                            const Extent &x, float (*tot)[64],
+                                            OpenList<CAP> &open,
+                                            const uint32_t *stop, uint32_t hb) {
+  const int lane = lane_here(), col = lane & 31, half = lane >> 5;
+  const float *C = half ? Y1 : X1;
+  const uint32_t one = half ? 0x00003f80u : 0x3f803f80u;
+  // in registers of their own: a scalar operand would halve the rate
+  float it = a.inv_tau, cc = half ? x.c1[1] : x.c1[0], kx = x.k2[0], ky = x.k2[1];
+  asm volatile("" : "+v"(it), "+v"(cc), "+v"(kx), "+v"(ky));
+  const uint32_t part_tile = n / 32u;   // the segment's partial tile, if it has one
+  const float part_ky = static_cast<uint32_t>(col) < n % 32u ? ky : __builtin_nanf("");
+  // coordinates of this lane's point of tile t, the index clamped into the segment
+  auto load = [&](uint32_t t, float &c, float &x2, float &y2) {
+    if (t < part_tile) {
+      const uint32_t at = t * 32u;   // scalar: only col is per lane
+      c = (C + at)[col];
+      x2 = (X2 + at)[col];
+      y2 = (Y2 + at)[col];
+    } else {
+      const uint32_t at = min(t * 32u + col, n - 1u);
+      c = C[at];
+      x2 = X2[at];
+      y2 = Y2[at];
+    }
+  };
+  float c, x2, y2;
+  load(t0, c, x2, y2);
+  for (uint32_t b0 = t0; b0 < t1; b0 += TB) {
+    if (stop &&
+        hb >= __hip_atomic_load(stop, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      return false;
+    const uint32_t b1 = min(b0 + TB, t1);
+    f32x16 s = {}, q = {};
+    for (uint32_t t = b0; t < b1; ++t) {
+      // past the last point of the segment: a NaN in y2c, so that t = 0
+      const float kt = t == part_tile ? part_ky : ky;
+      float cn, x2n, y2n;
+      load(t + 1u, cn, x2n, y2n);
+      const bf16x8 b = point_operand(c - cc, one);
+      const f32x16 zero = {};
+      const f32x16 u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(au, b, zero, 0, 0, 0);
+      const f32x16 w = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aw, b, zero, 0, 0, 0);
+      const f32x16 v = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, b, zero, 0, 0, 0);
+      const float xc = fmaf(x2, it, -kx), yc = fmaf(y2, it, -kt);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const float wj = w[i ^ 1];
+        const float ru = fmaf(-xc, wj, u[i]);
+        const float rv = fmaf(-yc, wj, v[i ^ 1]);
+        const float d = fmaf(rv, rv, fmaf(ru, ru, -0.5f));
+        // clamp to [0, 1], NaN to 0 (an output modifier of the FMA)
+        const float in = __builtin_amdgcn_fmed3f(fmaf(wj, wj, -d), 0.0f, 1.0f);
+        s[i] += in;
+        q[i ^ 1] = fmaf(in, in, q[i ^ 1]);
+      }
+      // whole register groups, so that q[i ^ 1] is not in the bank of result i
+      asm volatile("" : "+v"(s), "+v"(q));
+      c = cn;
+      x2 = x2n;
+      y2 = y2n;
+    }
+    uint64_t any = 0ull;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) any |= __ballot(s[i] != q[i ^ 1]);
+    if (any != 0ull) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        if (s[i] != q[i ^ 1]) {
+          const uint32_t m = m0 + 8u * (i / 4) + 4u * half + i % 4;
+          const uint32_t k = atomicAdd(&open.n, 1u);
+          if (k < CAP) {
+            open.e[k][0] = first_tile + b0;
+            open.e[k][1] = m | (static_cast<uint32_t>(col) << 6) | ((b1 - b0) << 11);
+          } else {
+            atomicOr(&open.lost[m >> 5], 1u << (m & 31u));
+          }
+          s[i] = 0.0f;
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tot[i][lane] += s[i];
+  }
+  return true;
 }
 
 // Adaptive stopping rule: with eps = best_count / n, enough samples have been
@@ -447,28 +704,13 @@ __device__ void adaptive_hint(const RansacArgs &a, int p, uint32_t n_pts, int HB
   atomicMin(&st->stop, s);
 }
 
-// Shared memory of one workgroup.
-template <int HB>
-struct Smem {
-  float H[HB][9];          // scoring form (rows 1-2 scaled by 1/tau)
-  double H0[HB][9];        // the float H, as doubles (for the float64 test)
-  uint32_t valid[HB];
-  uint32_t cnt[HB];
-  uint32_t ub[HB];         // scratch of fix_counts
-  FixList fix;             // groups to recount in float64
-  int64_t item;
-  uint32_t skip;
-};
-
-// Process one work item: pair rank r, hypothesis block hb (NW waves).
-template <int P, int HB, int NW>
-__device__ void run_item(const RansacArgs &a, int64_t item, Smem<HB> &sm) {
-  // pair-major items (all blocks of the largest pair first), or round-major
-  // under adaptive termination (round r of every pair before round r + 1)
+// Pair and round or hypothesis block of a work item: pair-major (all blocks of
+// the largest pair first), or under adaptive termination in the staggered
+// round order (ransac_round_order_kernel) or round-major.
+__device__ __forceinline__ void item_place(const RansacArgs &a, int64_t item, int &p, int &hb) {
   const bool adaptive = a.pst != nullptr;
-  int p, hb;
   if (adaptive && a.iorder) {
-    // staggered round order (ransac_round_order_kernel); decoded into range
+    // decoded into range
     const uint32_t code = static_cast<uint32_t>(a.iorder[item]);
     p = min(static_cast<int>(code / static_cast<uint32_t>(a.n_hb)), a.n_pairs - 1);
     hb = static_cast<int>(code % static_cast<uint32_t>(a.n_hb));
@@ -477,19 +719,304 @@ __device__ void run_item(const RansacArgs &a, int64_t item, Smem<HB> &sm) {
     hb = static_cast<int>(adaptive ? item / a.n_pairs : item % a.n_hb);
     p = a.order ? a.order[r] : r;
   }
-  int64_t base;
-  uint32_t n;
-  pair_range(a, p, base, n);
-  if (adaptive) {
-    // rounds at or past a known stopping point are not evaluated
-    if (threadIdx.x == 0)
-      sm.skip = static_cast<uint32_t>(hb) >=
-                __hip_atomic_load(&a.pst[p].stop, __ATOMIC_RELAXED, HG_AGENT);
-    __syncthreads();
-    const bool skip = sm.skip != 0u;
-    __syncthreads();
-    if (skip) return;
+}
+
+// Inliers of hypothesis lane % 32 over the tile loop's totals, in every lane:
+// lane l adds 16 of the 32 columns (rotated, so that the lanes of a bank read
+// different words).
+__device__ __forceinline__ uint32_t tile_count(const float (*tot)[64]) {
+  const int lane = lane_here();
+  const int m = lane & 31, i = (m >> 3) * 4 + (m & 3), h = (m >> 2) & 1;
+  uint32_t c = 0u;
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    c += static_cast<uint32_t>(tot[i][32 * h + 16 * (lane >> 5) + ((k + m) & 15)]);
+  return c + __shfl_xor(c, 32);
+}
+
+// The float64 test with H in memory as floats.
+__device__ __forceinline__ bool inlier_of(const float *H, float x1, float y1, float x2, float y2,
+                                          float tau) {
+  double g[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) g[k] = H[k];
+  return inlier_f64(g, x1, y1, x2, y2, tau);
+}
+
+// Float64 recount of a list's entries first, first + step, ... by one wave, TB
+// lanes to an entry; added to cnt.
+template <int TB, int CAP>
+__device__ __forceinline__ void count_open(const RansacArgs &a, const float *X1, const float *Y1,
+                                           const float *X2, const float *Y2, uint32_t n,
+                                           const float (*H)[9], const OpenList<CAP> &open,
+                                           uint32_t first, uint32_t step, uint32_t *cnt) {
+  const uint32_t lane = lane_here();
+  constexpr uint32_t kPer = 64u / TB;   // entries at a time
+  const uint32_t ne = min(open.n, static_cast<uint32_t>(CAP));
+  for (uint32_t k0 = first * kPer; k0 < ne; k0 += step * kPer) {
+    const uint32_t k = k0 + lane / TB;
+    bool in = false;
+    uint32_t h = 0u;
+    if (k < ne) {
+      const uint32_t w = open.e[k][1];
+      h = w & 63u;
+      const uint32_t j = lane % TB;
+      const uint32_t i = (open.e[k][0] + j) * 32u + ((w >> 6) & 31u);
+      if (j < ((w >> 11) & 63u) && i < n) in = inlier_of(H[h], X1[i], Y1[i], X2[i], Y2[i], a.tau);
+    }
+    const uint64_t b = __ballot(in) >> (lane / TB * TB);
+    if (lane % TB == 0u && k < ne) {
+      const uint32_t c = __popcll(b & ((1ull << TB) - 1ull));
+      if (c) atomicAdd(&cnt[h], c);
+    }
   }
+}
+
+// Float64 inliers of H among all points of the pair, by one wave.
+__device__ __forceinline__ uint32_t count_all(const RansacArgs &a, const float *X1, const float *Y1,
+                                              const float *X2, const float *Y2, uint32_t n,
+                                              const float *H) {
+  const uint32_t lane = lane_here();
+  uint32_t c = 0u;
+  for (uint32_t i = 0u; i < n; i += 64u) {
+    const uint32_t j = i + lane;
+    const uint32_t k = min(j, n - 1u);
+    c += __popcll(__ballot(inlier_of(H, X1[k], Y1[k], X2[k], Y2[k], a.tau) && j < n));
+  }
+  return c;
+}
+
+// Points per segment of the tile loop: 32-bit point offsets, and per-lane float
+// totals below 2^24.
+constexpr uint32_t kSegment = 1u << 28;
+
+// One item of the queue, placed: filled by one lane, read by the workgroup.
+struct ItemSlot {
+  int64_t item, base;
+  int32_t p, hb;
+  uint32_t n, skip;
+};
+
+// Shared memory of a workgroup that takes an item together (kWaves waves).
+constexpr int kGroupOpen = 1024;
+template <int HB>
+struct TileSmem {
+  static constexpr int HT = (HB + 31) / 32;
+  u32x4 op[HT][3][64];     // operand A of the three rows, by lane
+  float H0[HB][9];         // the float H (for the float64 test)
+  uint32_t valid[HB];
+  uint32_t full[HB];       // 1: counted in float64 throughout
+  uint32_t cnt[HB];
+  float tot[kWaves][16][64];   // per wave: inliers by result and lane
+  OpenList<kGroupOpen> open;
+  ItemSlot slot[2];
+};
+
+// Takes the next item from the queue (one lane).
+__device__ __forceinline__ void fetch_item(const RansacArgs &a, ItemSlot &s) {
+  const int64_t item = static_cast<int64_t>(atomicAdd(a.queue, 1u));
+  int p = 0, hb = 0;
+  int64_t base = 0;
+  uint32_t n = 0u;
+  if (item < a.n_items) {
+    item_place(a, item, p, hb);
+    pair_range(a, p, base, n);
+  }
+  s.item = item;
+  s.base = base;
+  s.p = p;
+  s.hb = hb;
+  s.n = n;
+}
+
+// Step 1, one wave: solve the item's hypotheses, one per lane, and lay out their
+// operands. Under adaptive termination a round at or past a known stopping
+// point is not evaluated (skip).
+template <int HB>
+__device__ __forceinline__ void group_solve(const RansacArgs &a, int64_t base, uint32_t n, int p,
+                                            int hb, TileSmem<HB> &sm, uint32_t &skip) {
+  const int t = lane_here();
+  const bool past = a.pst && static_cast<uint32_t>(hb) >=
+                                 __hip_atomic_load(&a.pst[p].stop, __ATOMIC_RELAXED, HG_AGENT);
+  if (t == 0) skip = past ? 1u : 0u;
+  if (past || t >= 32 * TileSmem<HB>::HT) return;
+  float h[9];
+  double g[9];
+  bool full;
+  const uint32_t f =
+      tile_hypothesis(a, base, n, p, hb * HB + t, t < min(HB, a.n_hyp - hb * HB), h, g, full);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    float x[3][3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) pieces(static_cast<float>(g[3 * r + k]), x[k]);
+    const int c = (t & 31) ^ (r ? 1 : 0);
+    sm.op[t >> 5][r][c] = row_operand(x[0], x[2], 0);
+    sm.op[t >> 5][r][c + 32] = row_operand(x[1], x[2], 1);
+  }
+  if (t < HB) {
+    if (f == 0u)
+#pragma unroll
+      for (int k = 0; k < 9; ++k) sm.H0[t][k] = h[k];
+    sm.valid[t] = f == 0u ? 1u : 0u;
+    sm.full[t] = full ? 1u : 0u;
+    sm.cnt[t] = 0u;
+  }
+  if (t == 0) sm.open.n = sm.open.lost[0] = sm.open.lost[1] = 0u;
+}
+
+// Step 2, every wave: its share of the pair's tiles against every hypothesis.
+template <int TB, int HB>
+__device__ __forceinline__ void group_score(const RansacArgs &a, int64_t base, uint32_t n, int p,
+                                            int hb, int wave, TileSmem<HB> &sm) {
+  const float *X1 = a.corr + base, *Y1 = a.corr + a.ld + base;
+  const float *X2 = a.corr + 2 * a.ld + base, *Y2 = a.corr + 3 * a.ld + base;
+  const uint32_t *stop = a.pst ? &a.pst[p].stop : nullptr;
+  const int lane = lane_here();
+  for (uint32_t seg = 0; seg < n; seg += kSegment) {
+    const uint32_t ns = min(n - seg, kSegment);
+    const uint32_t tiles = (ns + 31u) / 32u, share = (tiles + kWaves - 1u) / kWaves;
+    const uint32_t t0 = min(static_cast<uint32_t>(wave) * share, tiles), t1 = min(t0 + share, tiles);
+    for (int ht = 0; ht < TileSmem<HB>::HT && t0 < t1; ++ht) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sm.tot[wave][i][lane] = 0.0f;
+      if (!score_tiles<TB>(a, X1 + seg, Y1 + seg, X2 + seg, Y2 + seg, ns, t0, t1, seg / 32u,
+                           32u * ht, __builtin_bit_cast(bf16x8, sm.op[ht][0][lane]),
+                           __builtin_bit_cast(bf16x8, sm.op[ht][1][lane]),
+                           __builtin_bit_cast(bf16x8, sm.op[ht][2][lane]), a.extent[p],
+                           sm.tot[wave], sm.open, stop, static_cast<uint32_t>(hb)))
+        return;
+      const uint32_t c = tile_count(sm.tot[wave]);
+      if (lane < 32 && 32 * ht + lane < HB && c) atomicAdd(&sm.cnt[32 * ht + lane], c);
+    }
+  }
+}
+
+// Step 4, wave 0: an item's counts and its best key; c and ok: count and
+// validity of hypothesis hb HB + lane. Under adaptive termination a wave may
+// have given the round up: then it is at or past the stopping round (which
+// only decreases), and nothing of it is published.
+template <int HB>
+__device__ __forceinline__ void group_publish(const RansacArgs &a, int p, int hb, uint32_t n,
+                                              uint32_t c, bool ok) {
+  const int t = lane_here();
+  if (a.pst && static_cast<uint32_t>(hb) >=
+                   __hip_atomic_load(&a.pst[p].stop, __ATOMIC_RELAXED, HG_AGENT))
+    return;
+  const int h = hb * HB + t;
+  if (a.hyp_counts && t < HB && h < a.n_hyp)
+    a.hyp_counts[static_cast<int64_t>(p) * a.n_hyp + h] = ok ? static_cast<int32_t>(c) : 0;
+  const unsigned long long key = wave_max_u64(ok ? pack_key(c, static_cast<uint32_t>(h)) : 0ull);
+  if (t != 0) return;
+  if (a.pst) {
+    // write-once slot, then the advisory prefix / stopping hint
+    __hip_atomic_store(&a.rkey[static_cast<int64_t>(p) * a.n_hb + hb], key, __ATOMIC_RELAXED,
+                       HG_AGENT);
+    adaptive_hint(a, p, n, HB, hb, key);
+  } else if (key != 0ull) {
+    atomicMax(&a.keys[p], key);  // the pair's outputs come from the finish kernel
+  }
+}
+
+// A persistent workgroup, taking items of HB hypotheses of one pair together:
+// for adaptive termination, where fewer rounds in flight mean fewer past the
+// stopping points, and for launches of few items. In the fixed-count form an
+// item's serial steps run beside each other: while one of waves 1 - 3 solves its
+// hypotheses, another takes the next item from the queue and wave 0 publishes
+// the item before. Adaptive rounds are published at once, and the next is taken
+// only then (taken ahead, 512 pairs of up to 8000 points: 382 us, not 337, by
+// rounds that a fresher stopping hint would have skipped). Every lane-divergent
+// region is followed by a barrier before the loop closes, and every wave passes
+// the same barriers: the conditions around them are slot values read by all
+// after a barrier.
+template <int TB, int HB>
+__device__ __forceinline__ void group_loop(const RansacArgs &a, TileSmem<HB> &sm) {
+  const int lane = threadIdx.x & 63;
+  // scalar, so that the tile loop's counters and branches are
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  // different waves for workgroups that share a compute unit (and its SIMDs)
+  const int turn = static_cast<int>((blockIdx.x >> 8) % 3u);
+  const int solver = 1 + turn, fetcher = 1 + (turn + 1) % 3;
+  if (threadIdx.x == 0) fetch_item(a, sm.slot[0]);
+  __syncthreads();
+  // the item that wave 0 has yet to publish
+  int wait_p = -1, wait_hb = 0;
+  uint32_t wait_n = 0u, wait_c = 0u;
+  bool wait_ok = false;
+  for (int cur = 0;; cur ^= 1) {
+    const ItemSlot s = sm.slot[cur];
+    if (__builtin_amdgcn_readfirstlane(s.item >= a.n_items ? 1 : 0)) break;
+    const int p = __builtin_amdgcn_readfirstlane(s.p), hb = __builtin_amdgcn_readfirstlane(s.hb);
+    const uint32_t n = __builtin_amdgcn_readfirstlane(s.n);
+    const int64_t base = static_cast<int64_t>(
+        (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(
+             static_cast<int>(s.base >> 32)))) << 32) |
+        static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(s.base))));
+    if (wave == solver) {
+      group_solve<HB>(a, base, n, p, hb, sm, sm.slot[cur].skip);
+    } else if (wave == fetcher) {
+      if (lane == 0 && !a.pst) fetch_item(a, sm.slot[cur ^ 1]);
+    } else if (wave == 0 && wait_p >= 0) {
+      group_publish<HB>(a, wait_p, wait_hb, wait_n, wait_c, wait_ok);
+      wait_p = -1;
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(sm.slot[cur].skip) == 0u) {
+      group_score<TB, HB>(a, base, n, p, hb, wave, sm);
+      __syncthreads();
+      // 3. float64 counts: the listed points, then the hypotheses without a bound
+      // or with points lost to the list (after a barrier: they replace the counts)
+      const float *X1 = a.corr + base, *Y1 = a.corr + a.ld + base;
+      const float *X2 = a.corr + 2 * a.ld + base, *Y2 = a.corr + 3 * a.ld + base;
+      count_open<TB>(a, X1, Y1, X2, Y2, n, sm.H0, sm.open, static_cast<uint32_t>(wave), kWaves,
+                     sm.cnt);
+      __syncthreads();
+      const int nh = min(HB, a.n_hyp - hb * HB), t = lane < HB ? lane : 0;
+      for (uint64_t hm = __ballot(lane < nh && (sm.full[t] != 0u ||
+                                                ((sm.open.lost[t >> 5] >> (t & 31)) & 1u) != 0u));
+           hm; hm &= hm - 1ull) {
+        const int h = __ffsll(static_cast<long long>(hm)) - 1;
+        if (h % kWaves != wave) continue;
+        const uint32_t c = count_all(a, X1, Y1, X2, Y2, n, sm.H0[h]);
+        if (lane == 0) sm.cnt[h] = c;
+      }
+      __syncthreads();
+      if (wave == 0) {
+        const uint32_t c = sm.cnt[t];
+        const bool ok = lane < nh && sm.valid[t] != 0u;
+        if (a.pst) {
+          group_publish<HB>(a, p, hb, n, c, ok);
+        } else {
+          wait_p = p;
+          wait_hb = hb;
+          wait_n = n;
+          wait_c = c;
+          wait_ok = ok;
+        }
+      }
+    }
+    if (a.pst && threadIdx.x == 0) fetch_item(a, sm.slot[cur ^ 1]);
+    __syncthreads();
+  }
+  if (wave == 0 && wait_p >= 0) group_publish<HB>(a, wait_p, wait_hb, wait_n, wait_c, wait_ok);
+}
+
+// Shared memory of one workgroup of the fused single pair.
+template <int HB>
+struct Smem {
+  float H[HB][9];          // scoring form (rows 1-2 scaled by 1/tau)
+  double H0[HB][9];        // the float H, as doubles (for the float64 test)
+  uint32_t valid[HB];
+  uint32_t cnt[HB];
+  uint32_t ub[HB];         // scratch of fix_counts
+  FixList fix;             // groups to recount in float64
+};
+
+// Process one work item of the fused single pair: hypothesis block hb of HB
+// hypotheses (NW waves).
+template <int P, int HB, int NW>
+__device__ void run_item(const RansacArgs &a, int hb, Smem<HB> &sm) {
+  const uint32_t n = static_cast<uint32_t>(a.n_single);
   const int h0 = hb * HB;
   const int nh = min(HB, a.n_hyp - h0);
   // 1. solve this block's hypotheses, one per thread
@@ -498,14 +1025,12 @@ __device__ void run_item(const RansacArgs &a, int64_t item, Smem<HB> &sm) {
     uint32_t f = kZeroH;
     if (t < nh) {
       float h[9];
-      f = make_hypothesis(a.corr, a.ld, base, n, a.k0, a.k1, static_cast<uint32_t>(h0 + t),
-                          static_cast<uint32_t>(p), h);
+      f = make_hypothesis(a.corr, a.ld, 0, n, a.k0, a.k1, static_cast<uint32_t>(h0 + t), 0u, h);
       score_form(h, a.inv_tau, sm.H[t]);
 #pragma unroll
       for (int k = 0; k < 9; ++k) sm.H0[t][k] = h[k];
-      if (a.hbuf)
 #pragma unroll
-        for (int k = 0; k < 9; ++k) a.hbuf[9ll * (h0 + t) + k] = h[k];
+      for (int k = 0; k < 9; ++k) a.hbuf[9ll * (h0 + t) + k] = h[k];
     }
     sm.valid[t] = (t < nh && f == 0u) ? 1u : 0u;
     sm.cnt[t] = 0u;
@@ -515,21 +1040,9 @@ __device__ void run_item(const RansacArgs &a, int64_t item, Smem<HB> &sm) {
   // 2. score (validity as a wave-uniform bit mask)
   const int lane = threadIdx.x & 63;
   const uint64_t vmask = __ballot(lane < nh && sm.valid[lane] != 0u);
-  score_hyps<P, NW>(a, base, n, sm.H, vmask, nh, sm.cnt, &sm.fix,
-                adaptive ? &a.pst[p].stop : nullptr, static_cast<uint32_t>(hb));
+  score_hyps<P, NW>(a, 0, n, sm.H, vmask, nh, sm.cnt, &sm.fix);
   __syncthreads();
-  fix_counts<NW>(a, base, n, sm.H0, &sm.fix, vmask, nh, sm.cnt, a.hyp_counts != nullptr, sm.ub);
-  if (adaptive) {
-    // a wave may have given the round up: then it is at or past the stopping
-    // round (which only decreases), and nothing of it is published
-    if (threadIdx.x == 0)
-      sm.skip = static_cast<uint32_t>(hb) >=
-                __hip_atomic_load(&a.pst[p].stop, __ATOMIC_RELAXED, HG_AGENT);
-    __syncthreads();
-    const bool skip = sm.skip != 0u;
-    __syncthreads();
-    if (skip) return;
-  }
+  fix_counts<NW>(a, 0, n, sm.H0, &sm.fix, vmask, nh, sm.cnt, a.hyp_counts != nullptr, sm.ub);
   // 3. publish counts and the block's best key (wave 0 holds all HB <= 64)
   if (threadIdx.x < 64) {
     const int t = threadIdx.x;
@@ -537,47 +1050,26 @@ __device__ void run_item(const RansacArgs &a, int64_t item, Smem<HB> &sm) {
     if (t < nh) {
       const uint32_t c = sm.cnt[t];
       const bool ok = sm.valid[t] != 0u;
-      if (a.hyp_counts)
-        a.hyp_counts[static_cast<int64_t>(p) * a.n_hyp + h0 + t] = ok ? static_cast<int32_t>(c) : 0;
+      if (a.hyp_counts) a.hyp_counts[h0 + t] = ok ? static_cast<int32_t>(c) : 0;
       if (ok) key = pack_key(c, static_cast<uint32_t>(h0 + t));
     }
     key = wave_max_u64(key);
-    if (t == 0) {
-      if (a.blockbest) {
-        a.blockbest[item] = key;     // reduced by the mask kernel
-      } else if (adaptive) {
-        // write-once slot, then the advisory prefix / stopping hint
-        __hip_atomic_store(&a.rkey[static_cast<int64_t>(p) * a.n_hb + hb], key, __ATOMIC_RELAXED,
-                           HG_AGENT);
-        adaptive_hint(a, p, n, HB, hb, key);
-      } else if (key != 0ull) {
-        atomicMax(&a.keys[p], key);  // the pair's outputs come from the finish kernel
-      }
-    }
+    if (t == 0) a.blockbest[hb] = key;   // reduced by the mask kernel
   }
-  // Every wave leaves the item here together. Without this barrier the
-  // thread-0-only tail above may be folded into the persistent loop so that
-  // waves execute the loop's barriers different numbers of times.
-  __syncthreads();
 }
 
-// Persistent: kThreads threads, at least 5 workgroups per CU. Single pair
-// (one work item per workgroup): kFusedWaves waves, at least 2 per CU.
+// Persistent (P tiles between checks, HB hypotheses per item): kThreads
+// threads, 4 waves per SIMD (128 registers). Single pair (one work item per
+// workgroup): kFusedWaves waves, at least 2 per SIMD.
 template <int P, int HB, bool PERSISTENT>
-__global__ __launch_bounds__(PERSISTENT ? kThreads : kFusedWaves * 64, PERSISTENT ? 5 : 2)
+__global__ __launch_bounds__(PERSISTENT ? kThreads : kFusedWaves * 64, PERSISTENT ? 4 : 2)
 void ransac_kernel(RansacArgs a) {
-  __shared__ Smem<HB> sm;
-  if (!PERSISTENT) {
+  if constexpr (!PERSISTENT) {
+    __shared__ Smem<HB> sm;
     run_item<P, HB, kFusedWaves>(a, blockIdx.x, sm);
-    return;
-  }
-  for (;;) {
-    if (threadIdx.x == 0) sm.item = static_cast<int64_t>(atomicAdd(a.queue, 1u));
-    __syncthreads();
-    const int64_t item = sm.item;
-    __syncthreads();
-    if (item >= a.n_items) break;
-    run_item<P, HB, kWaves>(a, item, sm);
+  } else {
+    __shared__ TileSmem<HB> sm;
+    group_loop<P, HB>(a, sm);
   }
 }
 
@@ -728,16 +1220,88 @@ __global__ __launch_bounds__(kThreads) void ransac_mask_kernel(RansacArgs a) {
     a.mask[i] = (any && inlier_f64(hh, X1[i], Y1[i], X2[i], Y2[i], a.tau)) ? 1 : 0;
 }
 
+// The extent of a pair's points, by pair_waves waves per pair (1 or kWaves).
+__device__ void pair_extent(const RansacArgs &a, int block, int pair_waves) {
+  __shared__ float part[kWaves][8];
+  const int wave = threadIdx.x >> 6;
+  const bool solo = pair_waves == 1;
+  const int p = solo ? block * kWaves + wave : block;
+  int64_t base = 0;
+  uint32_t n = 0u;
+  if (p < a.n_pairs) pair_range(a, p, base, n);
+  const float *X[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) X[k] = a.corr + k * a.ld + base;
+  // maxima of x1, y1, x2, y2, then of their negatives
+  float m[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) m[k] = -__builtin_inff();
+  const uint32_t step = solo ? 64u : kThreads;
+  constexpr int kAhead = 8;   // points per thread whose loads are in flight together
+  for (uint64_t i0 = solo ? threadIdx.x & 63u : threadIdx.x; i0 < n; i0 += kAhead * step) {
+    float v[kAhead][4];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const uint64_t i = min(i0 + static_cast<uint64_t>(j) * step, static_cast<uint64_t>(n - 1u));
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[j][k] = X[k][i];
+    }
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      if (finite_f(v[j][0]) && finite_f(v[j][1]) && finite_f(v[j][2]) && finite_f(v[j][3])) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          m[k] = fmaxf(m[k], v[j][k]);
+          m[4 + k] = fmaxf(m[4 + k], -v[j][k]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) m[k] = wave_max_f32(m[k]);
+  if (!solo) {
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) part[wave][k] = m[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) m[k] = fmaxf(m[k], part[w][k]);
+  }
+  const bool writer = solo ? (threadIdx.x & 63) == 0 : threadIdx.x == 0;
+  if (!writer || p >= a.n_pairs) return;
+  constexpr float up = 1.0f + 9.5367432e-07f;   // above the rounding of the lines below
+  Extent x;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const bool none = !(m[0] > -__builtin_inff());
+    const float hi1 = none ? 0.0f : m[k], lo1 = none ? 0.0f : -m[4 + k];
+    const float hi2 = none ? 0.0f : m[2 + k], lo2 = none ? 0.0f : -m[6 + k];
+    x.c1[k] = 0.5f * lo1 + 0.5f * hi1;
+    x.k2[k] = (0.5f * lo2 + 0.5f * hi2) * a.inv_tau;
+    x.r1[k] = fmaxf(hi1 - x.c1[k], x.c1[k] - lo1) * up;
+    x.r2[k] = fmaxf(fmaf(hi2, a.inv_tau, -x.k2[k]), fmaf(-lo2, a.inv_tau, x.k2[k])) * up;
+  }
+  a.extent[p] = x;
+}
+
 // Resets keys, the queue and the adaptive state, and ranks pairs by size (largest
 // first, ties by index). Pair q's sort key is (N_q << 32) | ~q, unique per
 // pair, so the rank of p (the number of larger keys) is a permutation of
 // 0 .. n_pairs - 1. One wave ranks one pair; the keys are staged through LDS
 // in tiles of kThreads, shared by the workgroup's waves. Launched with one
-// wave per pair (at least one workgroup).
-__global__ __launch_bounds__(kThreads) void ransac_prep_kernel(RansacArgs a, int rank) {
+// wave per pair (at least one workgroup); the workgroups past n_prep take the
+// pairs' coordinate extents.
+__global__ __launch_bounds__(kThreads) void ransac_prep_kernel(RansacArgs a, int rank, int n_prep,
+                                                               int pair_waves) {
   __shared__ unsigned long long tile[kThreads];
+  if (static_cast<int>(blockIdx.x) >= n_prep) {
+    pair_extent(a, static_cast<int>(blockIdx.x) - n_prep, pair_waves);
+    return;
+  }
   const int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+  const int64_t stride = static_cast<int64_t>(n_prep) * blockDim.x;
   if (g == 0 && a.queue) *a.queue = 0u;
   for (int64_t q = g; q < a.n_pairs; q += stride) {
     if (a.keys) a.keys[q] = 0ull;
@@ -941,19 +1505,23 @@ static bool tune_valid(const hg_ransac_tuning &t) {
          t.blocks_per_cu >= 1 && t.blocks_per_cu <= 8;
 }
 
-static const hg_ransac_tuning kDefaultTune = {16, 64, 4, 0};
+static const hg_ransac_tuning kDefaultTune = {8, 64, 4, 0};
 
 typedef void (*KernelFn)(RansacArgs);
 
-template <bool PERSISTENT>
-static KernelFn pick_kernel(int P, int HB) {
-#define HG_PICK(PP, HH) \
-  if (P == PP && HB == HH) return ransac_kernel<PP, HH, PERSISTENT>;
-  HG_PICK(8, 4) HG_PICK(8, 8) HG_PICK(8, 16) HG_PICK(8, 32) HG_PICK(8, 64)
-  HG_PICK(16, 16) HG_PICK(16, 32) HG_PICK(16, 64)
-#undef HG_PICK
-  return nullptr;
+static KernelFn pick_fused(int HB) {
+  switch (HB) {
+    case 4: return ransac_kernel<8, 4, false>;
+    case 8: return ransac_kernel<8, 8, false>;
+    case 16: return ransac_kernel<8, 16, false>;
+    case 32: return ransac_kernel<8, 32, false>;
+    default: return ransac_kernel<8, 64, false>;
+  }
 }
+
+// Hypotheses of a work item: 32 or 64 (a tuning of 16 runs as 32, the height of a
+// tile).
+static int item_hyps(const hg_ransac_tuning &t) { return t.hyps_per_block == 64 ? 64 : 32; }
 
 static std::mutex g_tune_mu;
 static std::map<std::string, hg_ransac_tuning> g_tune_cache;
@@ -1002,11 +1570,22 @@ static void write_tune_file() {
   fclose(f);
 }
 
-static hg_ransac_tuning lookup_tune(int n_pairs, int n_hyp) {
+// The shape of a launch without an explicit tuning: the tuned one of this
+// problem, or the default with items of 64 hypotheses, halved where they would be
+// fewer than three to each resident workgroup and the pairs are large enough for
+// that to matter (64 pairs of up to 8000 points x 1024 hypotheses: 121 us with
+// 32, 135 us with 64; 512 pairs: 574 and 563 us; 64 pairs of up to 1000 points:
+// 61 and 60 us; 512 of up to 1000: 232 and 185 us).
+static hg_ransac_tuning lookup_tune(int n_pairs, int n_hyp, int64_t points) {
   std::lock_guard<std::mutex> lock(g_tune_mu);
   read_tune_file();
   auto it = g_tune_cache.find(tune_key(n_pairs, n_hyp));
-  return it == g_tune_cache.end() ? kDefaultTune : it->second;
+  if (it != g_tune_cache.end()) return it->second;
+  hg_ransac_tuning t = kDefaultTune;
+  const int64_t items = static_cast<int64_t>(n_pairs) * ((n_hyp + 63) / 64);
+  const bool large = points / n_pairs >= 1024;
+  if (items < (large ? 3072 : 512)) t.hyps_per_block = 32;
+  return t;
 }
 
 // ---- workspace layout ------------------------------------------------------
@@ -1017,10 +1596,12 @@ struct BatchedWs {
   unsigned long long *keys;
   int32_t *order;
   uint32_t *queue;
+  Extent *extent;
 };
 
 static size_t batched_ws_bytes(int n_pairs) {
-  return align256(8ull * n_pairs) + align256(4ull * n_pairs) + 256;
+  return align256(8ull * n_pairs) + align256(4ull * n_pairs) + 256 +
+         align256(sizeof(Extent) * static_cast<size_t>(n_pairs));
 }
 
 static BatchedWs carve_batched(void *ws, int n_pairs) {
@@ -1031,6 +1612,8 @@ static BatchedWs carve_batched(void *ws, int n_pairs) {
   w.order = reinterpret_cast<int32_t *>(p);
   p += align256(4ull * n_pairs);
   w.queue = reinterpret_cast<uint32_t *>(p);
+  p += 256;
+  w.extent = reinterpret_cast<Extent *>(p);
   return w;
 }
 
@@ -1087,6 +1670,7 @@ static RansacArgs make_args(const float *corr, int64_t ld, const int64_t *off, i
   a.pst = nullptr;
   a.rkey = nullptr;
   a.iorder = nullptr;
+  a.extent = nullptr;
   a.n_eval = nullptr;
   a.one_minus_conf = 0.0;
   return a;
@@ -1101,12 +1685,17 @@ static int launch_batched(const RansacArgs &a0, const hg_ransac_tuning &t, void 
   a.keys = w.keys;
   a.queue = w.queue;
   a.order = w.order;
+  a.extent = w.extent;
   const int rank = a.n_pairs <= 65536 ? 1 : 0;
   // one wave per pair when ranking (ranks of 65536 pairs: 16384 workgroups)
   const int64_t prep_blocks = rank ? (static_cast<int64_t>(a.n_pairs) + kWaves - 1) / kWaves
                                    : (static_cast<int64_t>(a.n_pairs) + kThreads - 1) / kThreads;
-  hipLaunchKernelGGL(ransac_prep_kernel, dim3(static_cast<unsigned>(prep_blocks)),
-                     dim3(kThreads), 0, s, a, rank);
+  // the extents: a workgroup per pair, or a wave where the pairs are small
+  const int pair_waves = a.ld / a.n_pairs >= 512 ? kWaves : 1;
+  const int64_t ext_blocks = pair_waves == 1 ? (static_cast<int64_t>(a.n_pairs) + kWaves - 1) / kWaves
+                                             : a.n_pairs;
+  hipLaunchKernelGGL(ransac_prep_kernel, dim3(static_cast<unsigned>(prep_blocks + ext_blocks)),
+                     dim3(kThreads), 0, s, a, rank, static_cast<int>(prep_blocks), pair_waves);
   if (int st = launched("ransac_prep_kernel")) return st;
   if (a.iorder) {
     const int64_t waves = static_cast<int64_t>(a.n_pairs) * a.n_hb;
@@ -1115,10 +1704,11 @@ static int launch_batched(const RansacArgs &a0, const hg_ransac_tuning &t, void 
                        dim3(kThreads), 0, s, a);
     if (int st = launched("ransac_round_order_kernel")) return st;
   }
-  KernelFn k = pick_kernel<true>(t.pts_per_lane, t.hyps_per_block);
-  if (!k) return fail(HG_EINVAL, "unsupported tuning");
   const int64_t blocks = std::min<int64_t>(static_cast<int64_t>(device_cus()) * t.blocks_per_cu,
                                            std::max<int64_t>(1, a.n_items));
+  const bool deep = t.pts_per_lane != 8;
+  auto *k = t.hyps_per_block == 64 ? (deep ? ransac_kernel<32, 64, true> : ransac_kernel<16, 64, true>)
+                                   : (deep ? ransac_kernel<32, 32, true> : ransac_kernel<16, 32, true>);
   hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, s, a);
   if (int st = launched("ransac_kernel<persistent>")) return st;
   hipLaunchKernelGGL(ransac_finish_kernel, dim3(static_cast<unsigned>(a.n_pairs)),
@@ -1173,13 +1763,12 @@ static int launch_fused(const float *corr, int32_t n_pts, int64_t ld, int32_t n_
   // about two workgroups per compute unit when the hypothesis count allows it
   int HB = 4;
   while (HB < 64 && static_cast<int64_t>(HB) * 2 * device_cus() < n_hyp) HB *= 2;
-  const int P = 8;
   RansacArgs a = make_args(corr, ld, nullptr, n_pts, 1, n_hyp, HB, thresh, seed, best_H,
                            best_count, best_hyp, inlier_mask, hyp_counts);
   char *w = static_cast<char *>(ws);
   a.hbuf = reinterpret_cast<float *>(w);
   a.blockbest = reinterpret_cast<unsigned long long *>(w + align256(36ull * n_hyp));
-  KernelFn k = pick_kernel<false>(P, HB);
+  KernelFn k = pick_fused(HB);
   hipLaunchKernelGGL(k, dim3(static_cast<unsigned>(a.n_items)), dim3(kFusedWaves * 64), 0, s, a);
   if (int st = launched("ransac_kernel<fused>")) return st;
   const int mb = std::max(1, std::min(1024, (n_pts + kThreads - 1) / kThreads));
@@ -1306,8 +1895,8 @@ extern "C" int hg_ransac_batched(const float *corr, int64_t ld, const int64_t *o
   if (int st = check_batched(corr, ld, off, n_pairs, n_hyp, thresh, tune, best_H, best_count,
                              best_hyp, inlier_mask, ws, ws_bytes))
     return st;
-  const hg_ransac_tuning t = tune ? *tune : lookup_tune(n_pairs, n_hyp);
-  RansacArgs a = make_args(corr, ld, off, 0, n_pairs, n_hyp, t.hyps_per_block, thresh, seed,
+  const hg_ransac_tuning t = tune ? *tune : lookup_tune(n_pairs, n_hyp, ld);
+  RansacArgs a = make_args(corr, ld, off, 0, n_pairs, n_hyp, item_hyps(t), thresh, seed,
                            best_H, best_count, best_hyp, inlier_mask, hyp_counts);
   return launch_batched(a, t, ws, as_stream(stream));
 }
@@ -1358,10 +1947,10 @@ extern "C" int hg_ransac_autotune(const float *corr, int64_t ld, const int64_t *
   hg_ransac_tuning best = kDefaultTune;
   int status = HG_OK;
   for (int P : {8, 16})
-    for (int HB : {16, 32, 64})
+    for (int HB : {32, 64})
       for (int bpc : {1, 2, 4, 5, 6}) {
         const hg_ransac_tuning t = {P, HB, bpc, 0};
-        RansacArgs a = make_args(corr, ld, off, 0, n_pairs, n_hyp, HB, thresh, seed, bh, bc, bi,
+        RansacArgs a = make_args(corr, ld, off, 0, n_pairs, n_hyp, item_hyps(t), thresh, seed, bh, bc, bi,
                                  mk, nullptr);
         if ((status = launch_batched(a, t, ws, s)) != HG_OK) goto done;   // warm-up
         float ms[3];
@@ -1431,7 +2020,7 @@ extern "C" int hg_ransac_adaptive(const float *corr, int64_t ld, const int64_t *
   if (ws_bytes < need)
     return fail(HG_EWORKSPACE, "hg_ransac_adaptive: workspace of %zu bytes needed, %zu given",
                 need, ws_bytes);
-  hg_ransac_tuning t = tune ? *tune : lookup_tune(n_pairs, n_hyp_max);
+  hg_ransac_tuning t = tune ? *tune : lookup_tune(n_pairs, n_hyp_max, ld);
   t.hyps_per_block = kRound;   // a work item is one round
   // without an explicit shape: at most 4 workgroups per CU (more rounds in
   // flight at once means more speculative rounds past the stopping points)
@@ -1462,8 +2051,8 @@ extern "C" int hg_ransac_batched_graph_create(const float *corr, int64_t ld, con
   if (int st = check_batched(corr, ld, off, n_pairs, n_hyp, thresh, tune, best_H, best_count,
                              best_hyp, inlier_mask, ws, ws_bytes))
     return st;
-  const hg_ransac_tuning t = tune ? *tune : lookup_tune(n_pairs, n_hyp);
-  RansacArgs a = make_args(corr, ld, off, 0, n_pairs, n_hyp, t.hyps_per_block, thresh, seed,
+  const hg_ransac_tuning t = tune ? *tune : lookup_tune(n_pairs, n_hyp, ld);
+  RansacArgs a = make_args(corr, ld, off, 0, n_pairs, n_hyp, item_hyps(t), thresh, seed,
                            best_H, best_count, best_hyp, inlier_mask, hyp_counts);
   return capture_graph(stream, [&](hipStream_t cap) { return launch_batched(a, t, ws, cap); },
                        out);
