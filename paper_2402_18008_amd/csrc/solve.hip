@@ -3,8 +3,20 @@
 // each of the 9 output planes (plus 64 flag bytes): memory-bound at 101 B per
 // quadruple, with the double-precision arithmetic hidden under the HBM time.
 // Measured on MI355X, this shape (512-thread workgroups, one quadruple per
-// lane, a grid that covers the batch once, non-temporal loads and stores)
-// streams faster than four quadruples per lane with 16-byte accesses.
+// lane, a grid that covers the batch once) streams faster than four quadruples
+// per lane with 16-byte accesses, except near n = 2^20, where all of their
+// workgroups are resident at once (25 us to 22; n = 3.2e6: 56 us to 66).
+//
+// Loads and stores are non-temporal while a wave's 256 bytes of a plane are
+// whole lines (STREAM). Where they are not, two waves share the line between
+// them, and a non-temporal access gives the line up after the first: it is
+// fetched twice, and written to memory as two partial lines. Ordinary accesses
+// let the second wave find it in L2, which joins the two writes. SKS solver,
+// planes n floats apart, non-temporal and ordinary: n = 512003, 15.2 and 14.1
+// us; 1024003, 27.8 and 25.6; 3200003, 74.8 and 65.1; 12800003, 302 and 247
+// (simplified SK 11.3 and 9.2, 19.5 and 19.3, 54.4 and 47.1, 217 and 174);
+// where the lines are whole the non-temporal accesses win (n = 3200000, 56.2
+// and 61.4; 12800000, 217 and 232).
 #include <cmath>
 
 #include "common.hpp"
@@ -14,7 +26,33 @@ namespace hg {
 
 constexpr int kSolveThreads = 512;
 
-template <int METHOD>
+template <bool STREAM, typename T>
+__device__ __forceinline__ T plane_load(const T *p) {
+  return STREAM ? __builtin_nontemporal_load(p) : *p;
+}
+
+template <bool STREAM, typename T>
+__device__ __forceinline__ void plane_store(T v, T *p) {
+  if (STREAM)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+// Whether every float plane starts on a 64-byte sector: one half of a line off
+// costs less than the ordinary accesses would (planes 64 k + 16 floats apart,
+// n = 1000003: 22.0 us against 22.7; simplified SK 15.5 against 16.5), a
+// quarter costs more at large n (64 k + 8, n = 4194309: 104 against 94.9; 73.2
+// against 69.0). A batch below kSharedLinesMin stays in the caches either way,
+// and the two differ by less than their own spread (n = 256003: 7.3 and 7.6 us).
+constexpr int64_t kSharedLinesMin = 1 << 18;
+static bool stream_planes(const void *a, const void *b, const void *c, int64_t n, int64_t ld) {
+  const uintptr_t bits = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) |
+                         reinterpret_cast<uintptr_t>(c) | static_cast<uintptr_t>(4 * ld);
+  return (bits & 63) == 0 || n <= kSharedLinesMin;
+}
+
+template <int METHOD, bool STREAM>
 __global__ __launch_bounds__(kSolveThreads) void solve4_kernel(const float *__restrict__ src,
                                                                const float *__restrict__ dst,
                                                                int64_t n, int64_t ld,
@@ -26,29 +64,30 @@ __global__ __launch_bounds__(kSolveThreads) void solve4_kernel(const float *__re
     float s[8], d[8], h[9];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      s[k] = __builtin_nontemporal_load(src + k * ld + q);
-      d[k] = __builtin_nontemporal_load(dst + k * ld + q);
+      s[k] = plane_load<STREAM>(src + k * ld + q);
+      d[k] = plane_load<STREAM>(dst + k * ld + q);
     }
     const uint32_t f = solve_quad<METHOD>(s, d, h);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) __builtin_nontemporal_store(h[k], H + k * ld + q);
-    if (flags) __builtin_nontemporal_store(static_cast<uint8_t>(f), flags + q);
+    for (int k = 0; k < 9; ++k) plane_store<STREAM>(h[k], H + k * ld + q);
+    if (flags) plane_store<STREAM>(static_cast<uint8_t>(f), flags + q);
   }
 }
 
-template <int METHOD>
+template <int METHOD, bool STREAM>
 static int launch_solve(const float *src, const float *dst, int64_t n, int64_t ld, float *H,
                         uint8_t *flags, hipStream_t s) {
   // one pass over the batch; beyond 2^31 - 1 workgroups the grid-stride loop takes over
   const int64_t blocks = (n + kSolveThreads - 1) / kSolveThreads;
   const unsigned grid = static_cast<unsigned>(blocks > 0x7FFFFFFF ? 0x7FFFFFFF : blocks);
-  hipLaunchKernelGGL(solve4_kernel<METHOD>, dim3(grid), dim3(kSolveThreads), 0, s, src, dst, n,
+  hipLaunchKernelGGL((solve4_kernel<METHOD, STREAM>), dim3(grid), dim3(kSolveThreads), 0, s, src, dst, n,
                      ld, H, flags);
   return launched("solve4_kernel");
 }
 
 // Simplified SK over n images of one pattern: 8 target planes in, 9 planes of
 // Hbar and the flags out (69 B per problem).
+template <bool STREAM>
 __global__ __launch_bounds__(kSolveThreads) void sk_kernel(SkPattern pat,
                                                            const float *__restrict__ dst,
                                                            int64_t n, int64_t ld,
@@ -59,16 +98,17 @@ __global__ __launch_bounds__(kSolveThreads) void sk_kernel(SkPattern pat,
        q += stride) {
     float d[8], h[9];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) d[k] = __builtin_nontemporal_load(dst + k * ld + q);
+    for (int k = 0; k < 8; ++k) d[k] = plane_load<STREAM>(dst + k * ld + q);
     const uint32_t f = solve_sk(pat, d, h);
 #pragma unroll
-    for (int k = 0; k < 9; ++k) __builtin_nontemporal_store(h[k], H + k * ld + q);
-    if (flags) __builtin_nontemporal_store(static_cast<uint8_t>(f), flags + q);
+    for (int k = 0; k < 9; ++k) plane_store<STREAM>(h[k], H + k * ld + q);
+    if (flags) plane_store<STREAM>(static_cast<uint8_t>(f), flags + q);
   }
 }
 
 // Three-point affine: 6 + 6 planes in, 6 planes of A and the flags out
 // (73 B per problem).
+template <bool STREAM>
 __global__ __launch_bounds__(kSolveThreads) void affine_kernel(const float *__restrict__ src,
                                                                const float *__restrict__ dst,
                                                                int64_t n, int64_t ld,
@@ -80,13 +120,13 @@ __global__ __launch_bounds__(kSolveThreads) void affine_kernel(const float *__re
     float s[6], d[6], a[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-      s[k] = __builtin_nontemporal_load(src + k * ld + q);
-      d[k] = __builtin_nontemporal_load(dst + k * ld + q);
+      s[k] = plane_load<STREAM>(src + k * ld + q);
+      d[k] = plane_load<STREAM>(dst + k * ld + q);
     }
     const uint32_t f = solve_affine(s, d, a);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) __builtin_nontemporal_store(a[k], A + k * ld + q);
-    if (flags) __builtin_nontemporal_store(static_cast<uint8_t>(f), flags + q);
+    for (int k = 0; k < 6; ++k) plane_store<STREAM>(a[k], A + k * ld + q);
+    if (flags) plane_store<STREAM>(static_cast<uint8_t>(f), flags + q);
   }
 }
 
@@ -136,8 +176,11 @@ extern "C" int hg_solve4(int method, const float *src, const float *dst, int64_t
              static_cast<long long>(n));
   HG_REQUIRE(ld <= (INT64_MAX / 16), "hg_solve4: ld too large");
   const hipStream_t s = hg::as_stream(stream);
-  return method == HG_ACA ? hg::launch_solve<0>(src, dst, n, ld, H, flags, s)
-                          : hg::launch_solve<1>(src, dst, n, ld, H, flags, s);
+  const auto launch = hg::stream_planes(src, dst, H, n, ld)
+                          ? (method == HG_ACA ? hg::launch_solve<0, true> : hg::launch_solve<1, true>)
+                          : (method == HG_ACA ? hg::launch_solve<0, false>
+                                              : hg::launch_solve<1, false>);
+  return launch(src, dst, n, ld, H, flags, s);
 }
 
 extern "C" int hg_solve_sk(const double *obj, const float *dst, int64_t n, int64_t ld, float *H,
@@ -153,7 +196,9 @@ extern "C" int hg_solve_sk(const double *obj, const float *dst, int64_t n, int64
   HG_REQUIRE(ld >= n, "hg_solve_sk: ld = %lld < n = %lld", static_cast<long long>(ld),
              static_cast<long long>(n));
   HG_REQUIRE(ld <= (INT64_MAX / 16), "hg_solve_sk: ld too large");
-  hipLaunchKernelGGL(hg::sk_kernel, dim3(hg::one_pass_grid(n)), dim3(hg::kSolveThreads), 0,
+  const auto kernel =
+      hg::stream_planes(dst, H, H, n, ld) ? hg::sk_kernel<true> : hg::sk_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3(hg::one_pass_grid(n)), dim3(hg::kSolveThreads), 0,
                      hg::as_stream(stream), pat, dst, n, ld, H, flags);
   return hg::launched("sk_kernel");
 }
@@ -167,7 +212,9 @@ extern "C" int hg_solve3_affine(const float *src, const float *dst, int64_t n, i
   HG_REQUIRE(ld >= n, "hg_solve3_affine: ld = %lld < n = %lld", static_cast<long long>(ld),
              static_cast<long long>(n));
   HG_REQUIRE(ld <= (INT64_MAX / 16), "hg_solve3_affine: ld too large");
-  hipLaunchKernelGGL(hg::affine_kernel, dim3(hg::one_pass_grid(n)), dim3(hg::kSolveThreads), 0,
+  const auto kernel = hg::stream_planes(src, dst, A, n, ld) ? hg::affine_kernel<true>
+                                                            : hg::affine_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3(hg::one_pass_grid(n)), dim3(hg::kSolveThreads), 0,
                      hg::as_stream(stream), src, dst, n, ld, A, flags);
   return hg::launched("affine_kernel");
 }
