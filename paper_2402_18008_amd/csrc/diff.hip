@@ -1076,20 +1076,21 @@ static RectArgs patch_rect(int h, int w) {
 }
 
 // Threads per patch workgroup: enough for about WAVES waves in flight over the
-// batch, from 256 threads up to MAXNT. The forward kernels aim at 8192 waves
-// (32 per CU) with up to 1024 threads; the backward ones at 4096 with up to
-// 512 (they would spill registers at 1024, and more waves did not help them).
-static int diff_threads(int B, int max_nt, int waves) {
+// batch, 256 or 512. The forward kernels aim at 8192 waves (32 per CU), the
+// backward ones at 4096 (more would spill registers and did not help). Forward
+// workgroups of 1024 threads are never better (512 patches of 100 x 100: 13.9
+// us, with 512 threads 11.9; 700 of 128 x 128: 29.3 and 24.4; 256 of 240 x 320:
+// 49.5 and 49.7).
+static int diff_threads(int B, int waves) {
   const int64_t want = (int64_t(waves) * 64 + B - 1) / std::max(B, 1);
-  const int nt = want <= 256 ? 256 : want <= 512 ? 512 : 1024;
-  return std::min(nt, max_nt);
+  return want <= 256 ? 256 : 512;
 }
 
 // Launch shape of a per-patch kernel: f(NT, ALIGNED) with NT from
 // diff_threads and ALIGNED = (NT is a multiple of the patch width w).
-template <int MAXNT = 1024, int WAVES = 8192, typename F>
+template <int WAVES = 8192, typename F>
 static void with_shape(int B, int w, F &&f) {
-  const int nt = diff_threads(B, MAXNT, WAVES);
+  const int nt = diff_threads(B, WAVES);
   const bool al = nt % w == 0;
   auto go = [&](auto NTc) {
     if (al)
@@ -1097,17 +1098,10 @@ static void with_shape(int B, int w, F &&f) {
     else
       f(NTc, std::false_type());
   };
-  if constexpr (MAXNT >= 1024) {
-    if (nt == 1024) {
-      go(std::integral_constant<int, 1024>());
-      return;
-    }
-  }
-  if (nt == 512) {
+  if (nt == 512)
     go(std::integral_constant<int, 512>());
-    return;
-  }
-  go(std::integral_constant<int, 256>());
+  else
+    go(std::integral_constant<int, 256>());
 }
 
 // Parts per patch: as many as give about 512 workgroups over the batch, or 768
@@ -1121,13 +1115,34 @@ static void with_shape(int B, int w, F &&f) {
 // leave compute units idle, more repeat the serial prologue (six steps on 64
 // patches of 128 x 128: 53 us with 512 workgroups, 61 us with 1024; on 128 of
 // 256 x 256: 146 us with 512, 134 us with 768, 144 us with 1024).
+//
+// A larger batch runs one workgroup per compute unit and, past 256 patches, a
+// second round, whose last part leaves units idle. Its patches are cut too, into
+// about 1536 workgroups, where the idle share of the chip times the iterations of
+// a patch is at least kPartMinIdle (up to two rounds). Loss and gradient in one
+// pass, forward alone, six steps; whole and cut, us: 160 of 300 x 300 (33 idle
+// iterations) 60 and 42, 54.5 and 34.3, 374 and 274; 218 of 240 x 320 (11.1) 53
+// and 46, 47.8 and 38.0, 331 and 300; 330 of 160 x 208 (11.7) 36.2 and 36.0,
+// 32.7 and 25.5, 250 and 228. Below it the repeated prologues cost more: 192 of
+// 200 x 200 (10) 25.8 and 28.0, 20.0 and 19.5, 184 and 179; 200 of 160 x 176 (6)
+// 19.0 and 23.6; 250 of 211 x 317 (1.5) six steps 295 and 299; 700 of 240 x 320
+// (6.6, third round) 132 and 139.
 constexpr int kPartMaxBatch = 128;
 constexpr int kPartMinIters = 8;
+constexpr int kPartMinIdle = 11;
 static PartShape split_parts(int B, int h, int w) {
   PartShape ps = {B, 1, 0};
   const int iters = (h * w + kPartPixels - 1) / kPartPixels;
-  if (B < 1 || B > kPartMaxBatch || iters < kPartMinIters) return ps;
-  const int groups = static_cast<int64_t>(iters) * B > 8 * 512 ? 768 : 512;
+  int groups;
+  if (B < 1 || iters < kPartMinIters) return ps;
+  if (B <= kPartMaxBatch) {
+    groups = static_cast<int64_t>(iters) * B > 8 * 512 ? 768 : 512;
+  } else {
+    constexpr int kUnits = 256;
+    const int slots = B <= kUnits ? kUnits : 2 * kUnits;
+    if (B > slots || static_cast<int64_t>(iters) * (slots - B) < kPartMinIdle * slots) return ps;
+    groups = 1536;
+  }
   const int want = std::min(iters, (groups + B - 1) / B);
   ps.per = (iters + want - 1) / want;
   ps.S = (iters + ps.per - 1) / ps.per;
@@ -1225,7 +1240,7 @@ static int launch_refine(const RefineArgs &a, const PartShape &ps, void *ws, hip
   if (ps.S > 1) return launch_refine_parts(a, ps, ws, s);
   const RectArgs ra = patch_rect(a.h, a.w);
   for (int it = 0; it < a.iters; ++it) {
-    with_shape<512, 4096>(a.B, a.w, [&](auto nt, auto al) {
+    with_shape<4096>(a.B, a.w, [&](auto nt, auto al) {
       constexpr int NT = decltype(nt)::value;
       constexpr bool AL = decltype(al)::value;
       hipLaunchKernelGGL((photo_bwd_kernel<true, NT, AL>), dim3(a.B), dim3(NT), 0, s, a.off,
@@ -1362,7 +1377,7 @@ extern "C" int hg_warp_l1_bwd_ws(const double *H, const float *img, const float 
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_warp_l1_bwd", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kGrad, false>(ps, H, nullptr, img, tgt, grad_loss, h, w, ws, nullptr, nullptr, grad_H, as_stream(stream));
-  with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((warp_kernel<kGrad, NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream), H,
@@ -1421,7 +1436,7 @@ extern "C" int hg_warp_bwd_from_grad(const double *H, const float *img, const fl
   if (int st = check_img(img, grad_warped, B, h, w, "hg_warp_bwd_from_grad")) return st;
   if (B == 0) return HG_OK;
   HG_REQUIRE(H && grad_H, "hg_warp_bwd_from_grad: NULL pointer");
-  with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((warp_kernel<kGradStored, NT, AL>), dim3(B), dim3(NT), 0,
@@ -1468,7 +1483,7 @@ extern "C" int hg_photometric_bwd_ws(const float *offsets, const float *img, con
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_bwd", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kGrad, true>(ps, nullptr, offsets, img, tgt, grad_loss, h, w, ws, nullptr, grad_offsets, nullptr, as_stream(stream));
-  with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((photo_bwd_kernel<false, NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream),
@@ -1496,7 +1511,7 @@ extern "C" int hg_photometric_fwd_grad_ws(const float *offsets, const float *img
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_fwd_grad", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kLossGrad, true>(ps, nullptr, offsets, img, tgt, nullptr, h, w, ws, loss, grad_unit, nullptr, as_stream(stream));
-  with_shape<512, 4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((photo_fwd_grad_kernel<NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream),

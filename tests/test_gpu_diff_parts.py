@@ -21,8 +21,9 @@ EINVAL, EWORKSPACE = -1, -3
 # (patches, height, width): widths that divide 256 and that do not; the smallest
 # patch that is cut and its neighbours; a last part of one row, of one pixel and
 # of a whole number of iterations; one patch over many parts; the largest batch
+# of a first round, and the batches of a part-filled first or second round
 SHAPES = [(1, 64, 113), (1, 57, 128), (3, 99, 83), (2, 113, 145), (1, 512, 512), (128, 128, 128),
-          (127, 97, 131), (5, 8193, 1), (7, 2, 4099)]
+          (127, 97, 131), (5, 8193, 1), (7, 2, 4099), (129, 145, 160), (257, 101, 239)]
 
 
 def _inputs(B, h, w, seed):
@@ -144,6 +145,9 @@ def test_workspace_limits():
     assert bool((ws[n:] == 0x5A).all())
     assert L.hg_photometric_ws_bytes(4, 16, 16) == 0 and L.hg_refine_ws_bytes(4, 16, 16) == 0
     assert L.hg_photometric_ws_bytes(4096, 128, 128) == 0
+    # 10 idle iterations (of 11), a full round, a third round
+    for b, hh, ww in ((192, 200, 200), (256, 256, 256), (513, 320, 320)):
+        assert L.hg_photometric_ws_bytes(b, hh, ww) == 0
     assert L.hg_photometric_ws_bytes(0, 128, 128) == 0
     assert L.hg_photometric_ws_bytes(1, 1 << 20, 1 << 20) == 0
     nr = L.hg_refine_ws_bytes(B, h, w)
