@@ -7,7 +7,8 @@
 // and h1 = (X^T X)^-1 X^T D_u X h3, h2 likewise with D_v.
 //
 // One workgroup per pair, one pass over the points (batches of 8 per thread,
-// loads issued ahead of use): the count and 29 moments of the coordinates
+// loads issued ahead of use; the 24 products enter their sums by fused
+// multiply-adds): the count and 29 moments of the coordinates
 // taken relative to the pair's first point, summed in double. One lane shifts
 // them to the centroids (binomial expansion: every moment needed for the shift
 // is among the 30 sums), the normalisation enters as powers of the two
@@ -30,11 +31,10 @@
 
 namespace hg {
 
-constexpr int kRefitThreads = 256;
 constexpr int kMoments = 29;   // centred: S0 5 (and the count), S1u, S2u, S1v, S2v 6 each
 constexpr int kRaw = 30;       // about the first point: 6 monomials each times 1, u, u^2, v, v^2
 
-// Points are visited kBatch at a time per thread (i0 + j * kRefitThreads),
+// Points are visited kBatch at a time per thread (i0 + j NT),
 // all their loads issued before any is used: one memory round trip per batch
 // instead of one per point. A thread's points keep their order, so the sums
 // do not depend on kBatch.
@@ -45,12 +45,13 @@ struct PointBatch {
   bool sel[kBatch];   // the point exists and its mask byte is set
 };
 
+template <int NT>
 __device__ __forceinline__ void load_batch(const float *X1, const float *Y1, const float *X2,
                                            const float *Y2, const uint8_t *mask, int64_t i0,
                                            int64_t b, PointBatch &pb) {
 #pragma unroll
   for (int j = 0; j < kBatch; ++j) {
-    const int64_t i = i0 + static_cast<int64_t>(j) * kRefitThreads;
+    const int64_t i = i0 + static_cast<int64_t>(j) * NT;
     const bool in = i < b;
     const int64_t ic = in ? i : b - 1;   // i0 < b, so every load stays inside the pair
     pb.x1[j] = X1[ic];
@@ -61,34 +62,39 @@ __device__ __forceinline__ void load_batch(const float *X1, const float *Y1, con
   }
 }
 
-// Workgroup sum of NV doubles; the result is valid in thread 0. Each row of 16
-// lanes sums its values (row_sum16_f64), then thread k adds the rows' partials
-// of value k in row order: a fixed order, so the result is deterministic.
-template <int NV>
+// Workgroup sum of NV doubles; the result is valid in thread 0. The values go
+// through LDS, kHalf of them at a time (30 KB; all at once would leave room for
+// two workgroups on a compute unit): lane (k, q) of the first 16 kHalf threads
+// adds the partials q, q + 16, ... of value k in that order, then the 16 lanes
+// of value k add their sums in row order. A fixed order, so the result is
+// deterministic; one row scan per value instead of one per value and row of
+// threads.
+template <int NV, int NT>
 __device__ __forceinline__ void refit_block_sum(double (&v)[NV]) {
-  constexpr int kRows = kRefitThreads / 16;
-  static_assert(NV <= kRefitThreads, "one thread per value");
-  __shared__ double red[NV][kRows];
+  constexpr int kHalf = 15, kPad = 16;   // padded: rows start 32 banks apart
+  static_assert(NV % kHalf == 0 && 16 * kHalf <= NT && NT % 16 == 0, "16 lanes per value");
+  __shared__ double part[kHalf][NT + kPad];
   __shared__ double tot[NV];
   const int t = threadIdx.x;
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const double s = row_sum16_f64(v[k]);
-    if ((t & 15) == 15) red[k][t >> 4] = s;
-  }
-  __syncthreads();
-  if (t < NV) {
-    double s = red[t][0];
+  for (int first = 0; first < NV; first += kHalf) {
 #pragma unroll
-    for (int r = 1; r < kRows; ++r) s += red[t][r];
-    tot[t] = s;
+    for (int k = 0; k < kHalf; ++k) part[k][t] = v[first + k];
+    __syncthreads();
+    if (t < 16 * kHalf) {
+      const int k = t / 16, q = t % 16;
+      double s = part[k][q];
+#pragma unroll
+      for (int j = 1; j < NT / 16; ++j) s += part[k][16 * j + q];
+      s = row_sum16_f64(s);
+      if (q == 15) tot[first + k] = s;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (t == 0) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) v[k] = tot[k];
   }
-  __syncthreads();
 }
 
 // Symmetric 3 x 3 from the six monomial sums m = {xx, xy, x, yy, y, 1} with
@@ -126,7 +132,8 @@ __host__ __device__ __forceinline__ void matmul3(const double A[3][3], const dou
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) C[i][j] = A[i][0] * B[0][j] + A[i][1] * B[1][j] + A[i][2] * B[2][j];
+    for (int j = 0; j < 3; ++j)
+      C[i][j] = fma(A[i][2], B[2][j], fma(A[i][1], B[1][j], A[i][0] * B[0][j]));
 }
 
 // Cyclic Jacobi eigenvalue iteration on a symmetric 3 x 3 (Golub and Van
@@ -185,64 +192,68 @@ __host__ __device__ inline void smallest_eigvec3(double A[3][3], double v[3]) {
 // Eigenvector of the smallest eigenvalue of a symmetric positive
 // semi-definite 3 x 3 C. Its adjugate has the same eigenvectors with the
 // eigenvalues l2 l3, l1 l3 and l1 l2 (0 <= l1 <= l2 <= l3), so the wanted
-// vector is adj(C)'s dominant one. Repeated squaring of adj(C) (rescaled to
-// max |entry| = 1 each time) squares the ratio l1 / l2 at every step, so the
-// matrix becomes rank one, every column parallel to the wanted vector; the
-// column of largest norm is taken once it stops changing direction. If that
-// does not happen within 12 squarings (l1 within ~0.1 % of l2: a
-// near-degenerate problem) the Jacobi iteration decides.
+// vector is adj(C)'s dominant one. Repeated squaring of adj(C) (rescaled by a
+// power of two each time) squares the ratio rho of the second eigenvalue to the
+// first at every step, so the matrix becomes rank one, every column parallel to
+// the wanted vector. With eigenvalues a >= b >= c >= 0, which any square has,
+// (tr A)^2 - tr A^2 = 2 (a b + a c + b c) >= 2 rho (tr A)^2 / 9: once that is at
+// most kRankOne tr A^2, A^2's own ratio is below 1e-17. If A = adj(C)^(2^11) still
+// has a ratio above ~1e-14 (l1 within 1.6 % of l2: a near-degenerate problem),
+// the Jacobi iteration decides. The vector is the column of largest norm, oriented like
+// that of the matrix before.
+// One lane runs this while its workgroup waits, so its dependent chain counts:
+// no division and no square root per squaring, and the norms of A's columns
+// and its trace test come with A^2 (512 pairs of 100 to 200 points: 13.2 us with
+// a normalised column compared at each step, 10.6 us so).
+constexpr double kRankOne = 6e-10, kRankOneLast = 2e-14;
+constexpr int kSquarings = 12;
 __host__ __device__ inline void smallest_eigvec3_adj(const double C[3][3], double v[3]) {
-  double A[3][3];
-  A[0][0] = C[1][1] * C[2][2] - C[1][2] * C[2][1];
-  A[0][1] = C[0][2] * C[2][1] - C[0][1] * C[2][2];
-  A[0][2] = C[0][1] * C[1][2] - C[0][2] * C[1][1];
-  A[1][1] = C[0][0] * C[2][2] - C[0][2] * C[2][0];
-  A[1][2] = C[0][2] * C[1][0] - C[0][0] * C[1][2];
-  A[2][2] = C[0][0] * C[1][1] - C[0][1] * C[1][0];
-  A[1][0] = A[0][1];
-  A[2][0] = A[0][2];
-  A[2][1] = A[1][2];
+  double a00 = C[1][1] * C[2][2] - C[1][2] * C[2][1];
+  double a01 = C[0][2] * C[2][1] - C[0][1] * C[2][2];
+  double a02 = C[0][1] * C[1][2] - C[0][2] * C[1][1];
+  double a11 = C[0][0] * C[2][2] - C[0][2] * C[2][0];
+  double a12 = C[0][2] * C[1][0] - C[0][0] * C[1][2];
+  double a22 = C[0][0] * C[1][1] - C[0][1] * C[1][0];
   double x[3] = {0.0, 0.0, 0.0};
   bool ok = false;
-  for (int it = 0; it < 13; ++it) {
-    double m = 0.0;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) m = fmax(m, fabs(A[i / 3][i % 3]));
+  for (int it = 0; it <= kSquarings; ++it) {
+    const double m = fmax(fmax(fmax(fabs(a00), fabs(a01)), fmax(fabs(a02), fabs(a11))),
+                          fmax(fabs(a12), fabs(a22)));
     if (!(m > 0.0) || !(m <= 1.7976931348623157e308)) break;
-    const double r = 1.0 / m;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) A[i / 3][i % 3] *= r;
-    // column of largest norm, scaled to max |component| = 1
-    int k = 0;
-    double best = -1.0;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const double s = A[0][j] * A[0][j] + A[1][j] * A[1][j] + A[2][j] * A[2][j];
-      if (s > best) {
-        best = s;
-        k = j;
-      }
-    }
-    double y[3] = {A[0][k], A[1][k], A[2][k]};
-    const double my = fmax(fabs(y[0]), fmax(fabs(y[1]), fabs(y[2])));
-    // orient like the previous estimate, then compare directions
-    double dot = y[0] * x[0] + y[1] * x[1] + y[2] * x[2];
-    const double sg = dot < 0.0 ? -1.0 / my : 1.0 / my;
-    double d = 0.0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      y[i] *= sg;
-      d = fmax(d, fabs(y[i] - x[i]));
-      x[i] = y[i];
-    }
-    if (it > 0 && d <= 1e-14) {
-      ok = true;
-      break;
-    }
-    double S[3][3];
-    matmul3(A, A, S);
-#pragma unroll
-    for (int i = 0; i < 9; ++i) A[i / 3][i % 3] = S[i / 3][i % 3];
+    int e;
+    (void)frexp(m, &e);
+    a00 = ldexp(a00, -e);
+    a01 = ldexp(a01, -e);
+    a02 = ldexp(a02, -e);
+    a11 = ldexp(a11, -e);
+    a12 = ldexp(a12, -e);
+    a22 = ldexp(a22, -e);
+    // A^2; its diagonal holds the squared norms of A's columns
+    const double s00 = fma(a02, a02, fma(a01, a01, a00 * a00));
+    const double s11 = fma(a12, a12, fma(a11, a11, a01 * a01));
+    const double s22 = fma(a22, a22, fma(a12, a12, a02 * a02));
+    const double s01 = fma(a02, a12, fma(a01, a11, a00 * a01));
+    const double s02 = fma(a02, a22, fma(a01, a12, a00 * a02));
+    const double s12 = fma(a12, a22, fma(a11, a12, a01 * a02));
+    const bool one = s11 > s00, two = s22 > (one ? s11 : s00);
+    double y0 = two ? a02 : one ? a01 : a00;
+    double y1 = two ? a12 : one ? a11 : a01;
+    double y2 = two ? a22 : one ? a12 : a02;
+    const bool flip = fma(y2, x[2], fma(y1, x[1], y0 * x[0])) < 0.0;
+    x[0] = flip ? -y0 : y0;
+    x[1] = flip ? -y1 : y1;
+    x[2] = flip ? -y2 : y2;
+    if (ok) break;   // the column of the square of a matrix that passed the test
+    const double tr = (a00 + a11) + a22, tr2 = (s00 + s11) + s22;
+    const double left = fma(tr, tr, -tr2);
+    ok = it > 0 && left <= (it < kSquarings - 1 ? kRankOne : kRankOneLast) * tr2;
+    if (it == kSquarings - 1 && !ok) break;
+    a00 = s00;
+    a01 = s01;
+    a02 = s02;
+    a11 = s11;
+    a12 = s12;
+    a22 = s22;
   }
   if (!ok) {
     double Cj[3][3];
@@ -353,7 +364,9 @@ __host__ __device__ inline void refit_solve(const double *m, double n, double cx
   }
 }
 
-__global__ __launch_bounds__(kRefitThreads) void refit_kernel(
+// NT threads, at least WAVES waves per SIMD.
+template <int NT, int WAVES>
+__global__ __launch_bounds__(NT, WAVES) void refit_kernel(
     const float *__restrict__ corr, int64_t ld, const int64_t *__restrict__ off,
     const uint8_t *__restrict__ mask, float *__restrict__ Hout, int32_t *__restrict__ n_used,
     uint8_t *__restrict__ flags) {
@@ -382,9 +395,9 @@ __global__ __launch_bounds__(kRefitThreads) void refit_kernel(
   auto moments = [&]() {
 #pragma unroll
     for (int k = 0; k < kRaw; ++k) r[k] = 0.0;
-    for (int64_t i0 = a + threadIdx.x; i0 < b; i0 += kRefitThreads * kBatch) {
+    for (int64_t i0 = a + threadIdx.x; i0 < b; i0 += NT * kBatch) {
       PointBatch pb;
-      load_batch(X1, Y1, X2, Y2, mask, i0, b, pb);
+      load_batch<NT>(X1, Y1, X2, Y2, mask, i0, b, pb);
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) {
         if (!pb.sel[j]) continue;
@@ -395,14 +408,14 @@ __global__ __launch_bounds__(kRefitThreads) void refit_kernel(
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
           r[k] += mono[k];
-          r[6 + k] += u * mono[k];
-          r[12 + k] += uu * mono[k];
-          r[18 + k] += v * mono[k];
-          r[24 + k] += vv * mono[k];
+          r[6 + k] = fma(u, mono[k], r[6 + k]);
+          r[12 + k] = fma(uu, mono[k], r[12 + k]);
+          r[18 + k] = fma(v, mono[k], r[18 + k]);
+          r[24 + k] = fma(vv, mono[k], r[24 + k]);
         }
       }
     }
-    refit_block_sum(r);
+    refit_block_sum<kRaw, NT>(r);
   };
   moments();
   // The shift to the centroids cancels about (distance / spread)^4 of the
@@ -414,9 +427,10 @@ __global__ __launch_bounds__(kRefitThreads) void refit_kernel(
     const double n0 = r[5];
     bool far = false;
     if (n0 >= 4.0) {
-      const double ma = r[2] / n0, mb = r[4] / n0, mc = r[11] / n0, md = r[23] / n0;
-      const double s1 = (r[0] + r[3]) / n0 - (ma * ma + mb * mb);
-      const double s2 = (r[17] + r[29]) / n0 - (mc * mc + md * md);
+      const double in = 1.0 / n0;
+      const double ma = r[2] * in, mb = r[4] * in, mc = r[11] * in, md = r[23] * in;
+      const double s1 = (r[0] + r[3]) * in - (ma * ma + mb * mb);
+      const double s2 = (r[17] + r[29]) * in - (mc * mc + md * md);
       far = !(ma * ma + mb * mb <= 16.0 * s1) || !(mc * mc + md * md <= 16.0 * s2);
       again[1] = rx + ma;
       again[2] = ry + mb;
@@ -456,6 +470,25 @@ __global__ __launch_bounds__(kRefitThreads) void refit_kernel(
   if (flags) flags[p] = static_cast<uint8_t>(f);
 }
 
+// A pair's time is a few dependent trips to memory (a batch of points each),
+// the workgroup sum and one lane's solve. Where all workgroups are resident at
+// once and the pairs have at least kLargePair points on average (of ld), 512
+// threads halve the trips (512 pairs of 4050 points on average: 22.8 us with 256
+// threads, 19.3 with 512; of 1050, 12.0 and 12.1; of 550, 10.0 and 10.8). More
+// pairs than three 256-thread workgroups per compute unit are held to 128
+// registers, so that four fit (1024 pairs of 1050 points: 18.2 and 15.5 us; 4096 of
+// 300: 39.9 and 36.8); fewer lose by it (256 pairs: 8.5 and 8.8 us).
+struct RefitShape {
+  decltype(&refit_kernel<256, 1>) kernel;
+  int threads;
+};
+static RefitShape refit_shape(int32_t n_pairs, int64_t ld) {
+  constexpr int64_t kLargePair = 1536;
+  if (n_pairs > 768) return {refit_kernel<256, 4>, 256};
+  if (n_pairs <= 512 && ld / n_pairs >= kLargePair) return {refit_kernel<512, 4>, 512};
+  return {refit_kernel<256, 1>, 256};
+}
+
 }  // namespace hg
 
 using namespace hg;
@@ -469,7 +502,8 @@ extern "C" int hg_refit_ho(const float *corr, int64_t ld, const int64_t *off, in
   HG_REQUIRE(corr && off && H, "hg_refit_ho: NULL corr, off or H");
   HG_REQUIRE(ld >= 1 && ld <= (INT64_MAX / 8), "hg_refit_ho: ld = %lld out of range",
              static_cast<long long>(ld));
-  hipLaunchKernelGGL(refit_kernel, dim3(n_pairs), dim3(kRefitThreads), 0, as_stream(stream), corr,
-                     ld, off, mask, H, n_used, flags);
+  const RefitShape k = refit_shape(n_pairs, ld);
+  hipLaunchKernelGGL(k.kernel, dim3(n_pairs), dim3(k.threads), 0, as_stream(stream), corr, ld, off,
+                     mask, H, n_used, flags);
   return launched("refit_kernel");
 }
