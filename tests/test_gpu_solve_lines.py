@@ -1,6 +1,7 @@
 """Large batches whose planes do not start on cache lines take ordinary instead
-of non-temporal accesses: the arithmetic is the same, so every plane and flag
-has the bits of the same batch laid out on whole lines."""
+of non-temporal accesses, and these and planes a multiple of 4 MB apart another
+order of workgroups: the arithmetic is the same, so every plane and flag has the
+bits of the same batch laid out on whole lines."""
 import pytest
 import torch
 
@@ -21,7 +22,10 @@ def layout(planes, ld, offset):
 @pytest.mark.parametrize("n,pad,offset", [(2**18, 1, 0),       # the largest that stays non-temporal
                                           (2**18 + 1, 0, 0),   # the smallest that does not
                                           (2**18 + 511, 1, 8),  # planes on a half sector
-                                          (300003, 13, 3)])
+                                          (300003, 13, 3),
+                                          (2**18, 2**20 - 2**18, 0),       # 4 MB apart
+                                          (2**18 + 1, 2**20 - 2**18 - 1, 0),
+                                          (400000, 2**20 - 400000, 0)])
 def test_misaligned_planes(solver, n, pad, offset):
     require_gpu()
     import paper_2402_18008_amd as hgpu
