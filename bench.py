@@ -420,8 +420,10 @@ def cpu_oracle_extras():
 
 
 FP32_FLOP_PER_HYP_PT = 21   # the division-free test as 21 FLOP (FMA = 2): 3 rows x 2 FMA,
-                            # 2 FMA residuals, mul + FMA norm, (tau w)^2; the kernel folds
-                            # tau into the operands and issues 12 VALU instructions
+                            # 2 FMA residuals, mul + FMA norm, (tau w)^2; the single-pair
+                            # kernel folds tau into the operands and issues 12 VALU
+                            # instructions, the many-pair kernel 7 and 1/16 of 3 MFMAs per
+                            # wave (so its share of the vector peak can pass 1)
 FP32_PEAK_TFLOPS = 157.3     # the published FP32 vector peak, for packed (two-wide) FP32
                              # instructions, which these kernels do not issue
 FP32_UNPACKED_TFLOPS = 78.6  # one FP32 FMA per lane and cycle: 256 CUs x 64 lanes x 2 x 2.4 GHz
