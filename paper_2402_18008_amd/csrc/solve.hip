@@ -54,28 +54,36 @@ static bool stream_planes(const void *a, const void *b, const void *c, int64_t n
 
 // Order of the workgroups over the batch. Consecutive workgroups go to the 8 XCDs
 // in turn, so in linear order every XCD touches every 16 KB of every plane. Grouped
-// order gives an XCD 32 consecutive workgroups (64 KB of each plane) of every 256.
-// It is taken where the planes' starts fall together: on planes that do not start
-// on lines, where neighbours share them and an XCD's L2 then holds both sides
-// (SKS solver, linear and grouped: n = 1000003, 23.7 and 22.9 us; 4194309, 98.3 and
-// 88.1; 12800003, 247 and 242; simplified SK 18.1 and 17.5, 73.8 and 64.4, 171 and
-// 163), and on planes a multiple of 4 MB apart up to 2^23 problems, whose accesses
-// meet in the same memory channels (n = 2^20, 24.6 and 21.4; 2^22, 86.4 and 82.9;
-// 5 2^20, 92 - 103 and 92; simplified SK 17.3 and 15.6, 62.6 and 57.5, 68 - 76 and
-// 63.5; 2^23, 109 - 118 and 97).
-// Elsewhere linear order streams better (n = 3200000, 56.4 and 57.1; 2^24, 278 and
-// 286; simplified SK 39.1 and 39.7, 188 and 193).
-constexpr uint32_t kGroup = 32, kXcds = 8;
-static uint32_t grouped_blocks(bool stream, int64_t n, int64_t ld, unsigned grid) {
+// order gives an XCD 2^log_group consecutive workgroups of every 8 times as many.
+// It is taken where the planes' starts fall together:
+//  * on planes that do not start on lines, where neighbours share them and an XCD's
+//    L2 then holds both sides; 32 workgroups (SKS solver, linear and grouped:
+//    n = 1000003, 23.7 and 22.9 us; 4194309, 98.3 and 88.1; 12800003, 247 and 242;
+//    simplified SK 18.1 and 17.5, 73.8 and 64.4, 171 and 163);
+//  * on planes a multiple of 4 MB apart up to 2^23 problems, whose accesses meet in
+//    the same memory channels; 256 workgroups (512 KB of each plane) between 2^20
+//    and 2^23, 32 at these ends (linear, 32 and 256; 2^20: 24.6, 22.0, 23.8; 2^21:
+//    44.6, 40.7, 38.2; 2^22: 86.4, 80.9, 71.4; 6 2^20: 116, 112, 108; simplified SK
+//    17.3, 15.8, 17.9; 32.4, 28.5, 26.7; 62.6, 57.9, 49.3; 85.2, 75.1, 71.8; 2^23:
+//    109 - 118, 98.2, 102).
+// Elsewhere linear order streams better (linear and 32: n = 3200000, 56.4 and 57.1;
+// 2^24, 278 and 286; simplified SK 39.1 and 39.7, 188 and 193).
+constexpr uint32_t kXcds = 8;
+struct BlockOrder {
+  uint32_t grouped;     // the workgroups that are permuted, in runs of kXcds 2^log_group
+  uint32_t log_group;
+};
+static BlockOrder block_order(bool stream, int64_t n, int64_t ld, unsigned grid) {
   const bool same_channels = ld % (1 << 20) == 0 && n > kSharedLinesMin && n <= (1 << 23);
-  return !stream || same_channels ? grid / (kXcds * kGroup) * (kXcds * kGroup) : 0u;
+  if (stream && !same_channels) return {0u, 0u};
+  const uint32_t lg = stream && n > (1 << 20) && n < (1 << 23) ? 8u : 5u;
+  return {grid >> lg >> 3 << lg << 3, lg};
 }
 
-// The first problem of a thread: the first grouped workgroups are permuted in
-// runs of kXcds kGroup.
-__device__ __forceinline__ int64_t first_problem(uint32_t grouped) {
-  const uint32_t b = blockIdx.x, in = b % (kXcds * kGroup);
-  const uint32_t tile = b < grouped ? b - in + in % kXcds * kGroup + in / kXcds : b;
+// The first problem of a thread.
+__device__ __forceinline__ int64_t first_problem(const BlockOrder &o) {
+  const uint32_t b = blockIdx.x, in = b & ((kXcds << o.log_group) - 1u);
+  const uint32_t tile = b < o.grouped ? b - in + (in % kXcds << o.log_group) + in / kXcds : b;
   return static_cast<int64_t>(tile) * kSolveThreads + threadIdx.x;
 }
 
@@ -83,11 +91,11 @@ template <int METHOD, bool STREAM>
 __global__ __launch_bounds__(kSolveThreads) void solve4_kernel(const float *__restrict__ src,
                                                                const float *__restrict__ dst,
                                                                int64_t n, int64_t ld,
-                                                               uint32_t grouped,
+                                                               BlockOrder order,
                                                                float *__restrict__ H,
                                                                uint8_t *__restrict__ flags) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t q = first_problem(grouped); q < n; q += stride) {
+  for (int64_t q = first_problem(order); q < n; q += stride) {
     float s[8], d[8], h[9];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -108,7 +116,7 @@ static int launch_solve(const float *src, const float *dst, int64_t n, int64_t l
   const int64_t blocks = (n + kSolveThreads - 1) / kSolveThreads;
   const unsigned grid = static_cast<unsigned>(blocks > 0x7FFFFFFF ? 0x7FFFFFFF : blocks);
   hipLaunchKernelGGL((solve4_kernel<METHOD, STREAM>), dim3(grid), dim3(kSolveThreads), 0, s, src, dst, n,
-                     ld, grouped_blocks(STREAM, n, ld, grid), H, flags);
+                     ld, block_order(STREAM, n, ld, grid), H, flags);
   return launched("solve4_kernel");
 }
 
@@ -117,11 +125,11 @@ static int launch_solve(const float *src, const float *dst, int64_t n, int64_t l
 template <bool STREAM>
 __global__ __launch_bounds__(kSolveThreads) void sk_kernel(SkPattern pat,
                                                            const float *__restrict__ dst,
-                                                           int64_t n, int64_t ld, uint32_t grouped,
+                                                           int64_t n, int64_t ld, BlockOrder order,
                                                            float *__restrict__ H,
                                                            uint8_t *__restrict__ flags) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t q = first_problem(grouped); q < n; q += stride) {
+  for (int64_t q = first_problem(order); q < n; q += stride) {
     float d[8], h[9];
 #pragma unroll
     for (int k = 0; k < 8; ++k) d[k] = plane_load<STREAM>(dst + k * ld + q);
@@ -137,11 +145,11 @@ __global__ __launch_bounds__(kSolveThreads) void sk_kernel(SkPattern pat,
 template <bool STREAM>
 __global__ __launch_bounds__(kSolveThreads) void affine_kernel(const float *__restrict__ src,
                                                                const float *__restrict__ dst,
-                                                               int64_t n, int64_t ld, uint32_t grouped,
+                                                               int64_t n, int64_t ld, BlockOrder order,
                                                                float *__restrict__ A,
                                                                uint8_t *__restrict__ flags) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-  for (int64_t q = first_problem(grouped); q < n; q += stride) {
+  for (int64_t q = first_problem(order); q < n; q += stride) {
     float s[6], d[6], a[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
@@ -225,7 +233,7 @@ extern "C" int hg_solve_sk(const double *obj, const float *dst, int64_t n, int64
   const unsigned grid = hg::one_pass_grid(n);
   hipLaunchKernelGGL((nt ? hg::sk_kernel<true> : hg::sk_kernel<false>), dim3(grid),
                      dim3(hg::kSolveThreads), 0, hg::as_stream(stream), pat, dst, n, ld,
-                     hg::grouped_blocks(nt, n, ld, grid), H, flags);
+                     hg::block_order(nt, n, ld, grid), H, flags);
   return hg::launched("sk_kernel");
 }
 
@@ -242,6 +250,6 @@ extern "C" int hg_solve3_affine(const float *src, const float *dst, int64_t n, i
   const unsigned grid = hg::one_pass_grid(n);
   hipLaunchKernelGGL((nt ? hg::affine_kernel<true> : hg::affine_kernel<false>), dim3(grid),
                      dim3(hg::kSolveThreads), 0, hg::as_stream(stream), src, dst, n, ld,
-                     hg::grouped_blocks(nt, n, ld, grid), A, flags);
+                     hg::block_order(nt, n, ld, grid), A, flags);
   return hg::launched("affine_kernel");
 }

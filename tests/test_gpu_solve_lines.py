@@ -25,7 +25,8 @@ def layout(planes, ld, offset):
                                           (300003, 13, 3),
                                           (2**18, 2**20 - 2**18, 0),       # 4 MB apart
                                           (2**18 + 1, 2**20 - 2**18 - 1, 0),
-                                          (400000, 2**20 - 400000, 0)])
+                                          (400000, 2**20 - 400000, 0),
+                                          (2**20 + 5, 2**20 - 5, 0)])      # large groups
 def test_misaligned_planes(solver, n, pad, offset):
     require_gpu()
     import paper_2402_18008_amd as hgpu
