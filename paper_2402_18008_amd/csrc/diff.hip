@@ -1078,19 +1078,24 @@ static RectArgs patch_rect(int h, int w) {
 // Threads per patch workgroup: enough for about WAVES waves in flight over the
 // batch, 256 or 512. The forward kernels aim at 8192 waves (32 per CU), the
 // backward ones at 4096 (more would spill registers and did not help). Forward
-// workgroups of 1024 threads are never better (512 patches of 100 x 100: 13.9
-// us, with 512 threads 11.9; 700 of 128 x 128: 29.3 and 24.4; 256 of 240 x 320:
-// 49.5 and 49.7).
-static int diff_threads(int B, int waves) {
+// workgroups have 1024 threads where one a compute unit has 12 to 63
+// iterations of 1024 pixels (512 and 1024 threads: 256 patches of 179 x 133, 16.9
+// and 14.9 us; 256 of 200 x 200, 24.3 and 20.6; 200 of 90 x 150, 10.7 and 10.3).
+// Smaller and larger patches, and larger batches, are as fast or faster with 512
+// (256 of 100 x 100, 8.5 and 8.7; 250 of 317 x 211, 44.6 and 51.8; 400 of 100 x
+// 100, 11.9 and 13.9; 700 of 128 x 128, 24.4 and 29.3).
+static int diff_threads(int B, int h, int w, int waves) {
   const int64_t want = (int64_t(waves) * 64 + B - 1) / std::max(B, 1);
+  const int64_t pixels = static_cast<int64_t>(h) * w;
+  if (waves >= 8192 && B <= 256 && pixels > 11 * 1024 && pixels <= 63 * 1024) return 1024;
   return want <= 256 ? 256 : 512;
 }
 
 // Launch shape of a per-patch kernel: f(NT, ALIGNED) with NT from
 // diff_threads and ALIGNED = (NT is a multiple of the patch width w).
 template <int WAVES = 8192, typename F>
-static void with_shape(int B, int w, F &&f) {
-  const int nt = diff_threads(B, WAVES);
+static void with_shape(int B, int h, int w, F &&f) {
+  const int nt = diff_threads(B, h, w, WAVES);
   const bool al = nt % w == 0;
   auto go = [&](auto NTc) {
     if (al)
@@ -1098,6 +1103,12 @@ static void with_shape(int B, int w, F &&f) {
     else
       f(NTc, std::false_type());
   };
+  if constexpr (WAVES >= 8192) {
+    if (nt == 1024) {
+      go(std::integral_constant<int, 1024>());
+      return;
+    }
+  }
   if (nt == 512)
     go(std::integral_constant<int, 512>());
   else
@@ -1240,7 +1251,7 @@ static int launch_refine(const RefineArgs &a, const PartShape &ps, void *ws, hip
   if (ps.S > 1) return launch_refine_parts(a, ps, ws, s);
   const RectArgs ra = patch_rect(a.h, a.w);
   for (int it = 0; it < a.iters; ++it) {
-    with_shape<4096>(a.B, a.w, [&](auto nt, auto al) {
+    with_shape<4096>(a.B, a.h, a.w, [&](auto nt, auto al) {
       constexpr int NT = decltype(nt)::value;
       constexpr bool AL = decltype(al)::value;
       hipLaunchKernelGGL((photo_bwd_kernel<true, NT, AL>), dim3(a.B), dim3(NT), 0, s, a.off,
@@ -1249,7 +1260,7 @@ static int launch_refine(const RefineArgs &a, const PartShape &ps, void *ws, hip
     if (int st = launched("photo_bwd_kernel<step>")) return st;
   }
   if (a.loss) {
-    with_shape(a.B, a.w, [&](auto nt, auto al) {
+    with_shape(a.B, a.h, a.w, [&](auto nt, auto al) {
       constexpr int NT = decltype(nt)::value;
       constexpr bool AL = decltype(al)::value;
       hipLaunchKernelGGL((photo_fwd_kernel<NT, AL>), dim3(a.B), dim3(NT), 0, s, a.off, a.img,
@@ -1352,7 +1363,7 @@ extern "C" int hg_warp_l1_fwd_ws(const double *H, const float *img, const float 
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_warp_l1_fwd", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kLoss, false>(ps, H, nullptr, img, tgt, nullptr, h, w, ws, loss, nullptr, nullptr, as_stream(stream));
-  with_shape(B, w, [&](auto nt, auto al) {
+  with_shape(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((warp_kernel<kLoss, NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream), H,
@@ -1377,7 +1388,7 @@ extern "C" int hg_warp_l1_bwd_ws(const double *H, const float *img, const float 
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_warp_l1_bwd", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kGrad, false>(ps, H, nullptr, img, tgt, grad_loss, h, w, ws, nullptr, nullptr, grad_H, as_stream(stream));
-  with_shape<4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((warp_kernel<kGrad, NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream), H,
@@ -1398,7 +1409,7 @@ extern "C" int hg_warp_store_fwd(const double *H, const float *img, int32_t B, i
   if (int st = check_img(img, warped, B, h, w, "hg_warp_store_fwd")) return st;
   if (B == 0) return HG_OK;
   HG_REQUIRE(H, "hg_warp_store_fwd: NULL H");
-  with_shape(B, w, [&](auto nt, auto al) {
+  with_shape(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((warp_kernel<kStore, NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream), H,
@@ -1436,7 +1447,7 @@ extern "C" int hg_warp_bwd_from_grad(const double *H, const float *img, const fl
   if (int st = check_img(img, grad_warped, B, h, w, "hg_warp_bwd_from_grad")) return st;
   if (B == 0) return HG_OK;
   HG_REQUIRE(H && grad_H, "hg_warp_bwd_from_grad: NULL pointer");
-  with_shape<4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((warp_kernel<kGradStored, NT, AL>), dim3(B), dim3(NT), 0,
@@ -1457,7 +1468,7 @@ extern "C" int hg_photometric_fwd_ws(const float *offsets, const float *img, con
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_fwd", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kLoss, true>(ps, nullptr, offsets, img, tgt, nullptr, h, w, ws, loss, nullptr, nullptr, as_stream(stream));
-  with_shape(B, w, [&](auto nt, auto al) {
+  with_shape(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((photo_fwd_kernel<NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream),
@@ -1483,7 +1494,7 @@ extern "C" int hg_photometric_bwd_ws(const float *offsets, const float *img, con
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_bwd", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kGrad, true>(ps, nullptr, offsets, img, tgt, grad_loss, h, w, ws, nullptr, grad_offsets, nullptr, as_stream(stream));
-  with_shape<4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((photo_bwd_kernel<false, NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream),
@@ -1511,7 +1522,7 @@ extern "C" int hg_photometric_fwd_grad_ws(const float *offsets, const float *img
   if (int st = use_parts(B, h, w, ws, ws_bytes, false, "hg_photometric_fwd_grad", ps)) return st;
   if (ps.S > 1)
     return launch_parts<kLossGrad, true>(ps, nullptr, offsets, img, tgt, nullptr, h, w, ws, loss, grad_unit, nullptr, as_stream(stream));
-  with_shape<4096>(B, w, [&](auto nt, auto al) {
+  with_shape<4096>(B, h, w, [&](auto nt, auto al) {
     constexpr int NT = decltype(nt)::value;
     constexpr bool AL = decltype(al)::value;
     hipLaunchKernelGGL((photo_fwd_grad_kernel<NT, AL>), dim3(B), dim3(NT), 0, as_stream(stream),
