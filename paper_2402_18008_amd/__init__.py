@@ -7,6 +7,7 @@ in the library's HIP kernels. Function names match the C entry points.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import functools
 
@@ -28,6 +29,32 @@ __all__ = ["hg_solve4", "solve4", "HomogError", "HG_ACA", "HG_SKS"]
 def _stream(stream=None):
     s = torch.cuda.current_stream() if stream is None else stream
     return s.cuda_stream
+
+
+def _pool(stream, device):
+    """Context in which torch allocates from the pool of ``stream`` (None: the
+    current stream), which may be any object with a ``cuda_stream`` handle. What a
+    call on ``stream`` writes comes from there: the allocator hands a freed block out
+    again in the order of the stream it was allocated on, and memory from another
+    stream's pool may still be written by what is queued there."""
+    if stream is None or stream.cuda_stream == torch.cuda.current_stream(device).cuda_stream:
+        return contextlib.nullcontext()
+    if not isinstance(stream, torch.cuda.Stream):
+        raw = stream.cuda_stream
+        stream = (torch.cuda.ExternalStream(raw, device=device) if raw
+                  else torch.cuda.default_stream(device))
+    return torch.cuda.stream(stream)
+
+
+def _new(stream, device, *specs):
+    """Outputs of (size, dtype) of a call on ``stream``, from its pool; the allocator
+    keeps a dropped one until what the current stream did with it has run."""
+    with _pool(stream, device):
+        new = [torch.empty(size, dtype=dtype, device=device) for size, dtype in specs]
+    if stream is not None:
+        for t in new:
+            t.record_stream(torch.cuda.current_stream(device))
+    return new
 
 
 def _dev(t, name, dtype=torch.float32):
@@ -61,11 +88,11 @@ def hg_solve4(src, dst, method=HG_ACA, H=None, flags=None, stream=None):
         raise ValueError("src and dst must share the plane stride")
     n = src.shape[1]
     if H is None:
-        H = torch.empty((9, ld), dtype=torch.float32, device=src.device)[:, :n]
+        H = _new(stream, src.device, ((9, ld), torch.float32))[0][:, :n]
     elif _planes(H, "H", 9) != ld:
         raise ValueError("H must share the plane stride of src")
     if flags is None:
-        flags = torch.empty(n, dtype=torch.uint8, device=src.device)
+        (flags,) = _new(stream, src.device, (n, torch.uint8))
     _dev(flags, "flags", torch.uint8)
     _abi.call("hg_solve4", int(method), src.data_ptr(), dst.data_ptr(), n, ld, H.data_ptr(),
               flags.data_ptr(), _stream(stream))
@@ -89,11 +116,11 @@ def hg_solve_sk(obj, dst, H=None, flags=None, stream=None):
     ld = _planes(dst, "dst", 8)
     n = dst.shape[1]
     if H is None:
-        H = torch.empty((9, ld), dtype=torch.float32, device=dst.device)[:, :n]
+        H = _new(stream, dst.device, ((9, ld), torch.float32))[0][:, :n]
     elif _planes(H, "H", 9) != ld:
         raise ValueError("H must share the plane stride of dst")
     if flags is None:
-        flags = torch.empty(n, dtype=torch.uint8, device=dst.device)
+        (flags,) = _new(stream, dst.device, (n, torch.uint8))
     _dev(flags, "flags", torch.uint8)
     _abi.call("hg_solve_sk", o, dst.data_ptr(), n, ld, H.data_ptr(), flags.data_ptr(), frame,
               _stream(stream))
@@ -112,11 +139,11 @@ def hg_solve3_affine(src, dst, A=None, flags=None, stream=None):
         raise ValueError("src and dst must share the plane stride")
     n = src.shape[1]
     if A is None:
-        A = torch.empty((6, ld), dtype=torch.float32, device=src.device)[:, :n]
+        A = _new(stream, src.device, ((6, ld), torch.float32))[0][:, :n]
     elif _planes(A, "A", 6) != ld:
         raise ValueError("A must share the plane stride of src")
     if flags is None:
-        flags = torch.empty(n, dtype=torch.uint8, device=src.device)
+        (flags,) = _new(stream, src.device, (n, torch.uint8))
     _dev(flags, "flags", torch.uint8)
     _abi.call("hg_solve3_affine", src.data_ptr(), dst.data_ptr(), n, ld, A.data_ptr(),
               flags.data_ptr(), _stream(stream))
@@ -130,7 +157,7 @@ def hg_stream_copy(src, dst=None, stream=None):
     if not src.is_contiguous():
         raise ValueError("src must be contiguous")
     if dst is None:
-        dst = torch.empty_like(src)
+        (dst,) = _new(stream, src.device, (src.shape, torch.float32))
     _abi.call("hg_stream_copy", src.data_ptr(), dst.data_ptr(), src.numel(), _stream(stream))
     return dst
 
@@ -146,7 +173,7 @@ def hg_stream_planes(inp, n_out, out=None, flags=None, stream=None):
     n_in, n = inp.shape
     ld = inp.stride(0)
     if out is None:
-        out = torch.empty((n_out, ld), dtype=torch.float32, device=inp.device)[:, :n]
+        out = _new(stream, inp.device, ((n_out, ld), torch.float32))[0][:, :n]
     if out.shape != (n_out, n) or out.stride() != (ld, 1):
         raise ValueError("out must be (n_out, n) with the plane stride of inp")
     _dev(out, "out")
@@ -170,14 +197,22 @@ def hg_ransac_ws_bytes(n_pts, n_hyp):
     return int(_abi.lib().hg_ransac_ws_bytes(int(n_pts), int(n_hyp)))
 
 
-def _ws(nbytes, device, ws):
+def _ws(nbytes, device, ws, stream=None):
     if ws is None:
         # 256-byte aligned: torch's caching allocator returns aligned blocks
-        ws = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        with _pool(stream, device):
+            ws = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
     _dev(ws, "ws", torch.uint8)
     if ws.numel() < nbytes:
         raise ValueError(f"workspace of {nbytes} bytes needed, {ws.numel()} given")
     return ws
+
+
+def _ransac_out(n, n_hyp, want_counts, device, stream):
+    specs = [(9, torch.float32), (1, torch.int32), (1, torch.int32), (n, torch.uint8)]
+    new = _new(stream, device, *specs, *([(n_hyp, torch.int32)] if want_counts else []))
+    return dict(zip(("best_H", "best_count", "best_hyp", "mask", "hyp_counts"),
+                    new if want_counts else (*new, None)))
 
 
 def _ransac(name, corr, n_hyp, thresh, seed, want_counts, ws, stream):
@@ -187,13 +222,8 @@ def _ransac(name, corr, n_hyp, thresh, seed, want_counts, ws, stream):
         return r
     ld, n = _corr_planes(corr)
     dev = corr.device
-    ws = _ws(hg_ransac_ws_bytes(n, n_hyp), dev, ws)
-    out = dict(best_H=torch.empty(9, dtype=torch.float32, device=dev),
-               best_count=torch.empty(1, dtype=torch.int32, device=dev),
-               best_hyp=torch.empty(1, dtype=torch.int32, device=dev),
-               mask=torch.empty(n, dtype=torch.uint8, device=dev),
-               hyp_counts=(torch.empty(n_hyp, dtype=torch.int32, device=dev)
-                           if want_counts else None))
+    ws = _ws(hg_ransac_ws_bytes(n, n_hyp), dev, ws, stream)
+    out = _ransac_out(n, n_hyp, want_counts, dev, stream)
     hc = out["hyp_counts"]
     _abi.call(name, corr.data_ptr(), n, ld, int(n_hyp), float(thresh), int(seed) & (2**64 - 1),
               out["best_H"].data_ptr(), out["best_count"].data_ptr(), out["best_hyp"].data_ptr(),
@@ -223,12 +253,7 @@ def hg_ransac_noalloc(corr, n_hyp, thresh, seed, hyp_counts=True, out=None, stre
     ld, n = _corr_planes(corr)
     dev = corr.device
     if out is None:
-        out = dict(best_H=torch.empty(9, dtype=torch.float32, device=dev),
-                   best_count=torch.empty(1, dtype=torch.int32, device=dev),
-                   best_hyp=torch.empty(1, dtype=torch.int32, device=dev),
-                   mask=torch.empty(n, dtype=torch.uint8, device=dev),
-                   hyp_counts=(torch.empty(n_hyp, dtype=torch.int32, device=dev)
-                               if hyp_counts else None))
+        out = _ransac_out(n, n_hyp, hyp_counts, dev, stream)
     hc = out["hyp_counts"]
     _abi.call("hg_ransac_noalloc", corr.data_ptr(), n, ld, int(n_hyp), float(thresh),
               int(seed) & (2**64 - 1), out["best_H"].data_ptr(), out["best_count"].data_ptr(),
@@ -302,9 +327,9 @@ def hg_refit_ho(corr, off, mask=None, H=None, n_used=None, flags=None, stream=No
     H = _out(H, "H", torch.float32, 9 * n_pairs, dev)
     n_used = _out(n_used, "n_used", torch.int32, n_pairs, dev)
     flags = _out(flags, "flags", torch.uint8, n_pairs, dev)
-    H = torch.empty((n_pairs, 9), dtype=torch.float32, device=dev) if H is None else H
-    n_used = torch.empty(n_pairs, dtype=torch.int32, device=dev) if n_used is None else n_used
-    flags = torch.empty(n_pairs, dtype=torch.uint8, device=dev) if flags is None else flags
+    H = _new(stream, dev, ((n_pairs, 9), torch.float32))[0] if H is None else H
+    n_used = _new(stream, dev, (n_pairs, torch.int32))[0] if n_used is None else n_used
+    flags = _new(stream, dev, (n_pairs, torch.uint8))[0] if flags is None else flags
     _abi.call("hg_refit_ho", corr.data_ptr(), ld, off.data_ptr(), n_pairs,
               mask.data_ptr() if mask is not None else None, H.data_ptr(), n_used.data_ptr(),
               flags.data_ptr(), _stream(stream))
@@ -407,7 +432,7 @@ class Graph:
     def launch(self, stream=None):
         raw = _stream(stream)
         if isinstance(self.owner, Refine):
-            self.owner._record(raw, stream)
+            self.owner._ready(raw, stream)
         _abi.call("hg_graph_launch", self.h, raw)
 
     def close(self):
@@ -451,7 +476,7 @@ def hg_aca_rect_fwd(offsets, x0, y0, w, r, stream=None):
         return out
     _c(offsets, "offsets")
     B = offsets.shape[0]
-    H = torch.empty((B, 9), dtype=torch.float64, device=offsets.device)
+    (H,) = _new(stream, offsets.device, ((B, 9), torch.float64))
     _abi.call("hg_aca_rect_fwd", offsets.data_ptr(), B, float(x0), float(y0), float(w), float(r),
               H.data_ptr(), _stream(stream))
     return H
@@ -464,7 +489,7 @@ def hg_aca_rect_bwd(offsets, grad_H, x0, y0, w, r, stream=None):
     _c(offsets, "offsets")
     _c(grad_H, "grad_H", torch.float64)
     B = offsets.shape[0]
-    g = torch.empty((B, 4, 2), dtype=torch.float32, device=offsets.device)
+    (g,) = _new(stream, offsets.device, ((B, 4, 2), torch.float32))
     _abi.call("hg_aca_rect_bwd", offsets.data_ptr(), grad_H.data_ptr(), B, float(x0), float(y0),
               float(w), float(r), g.data_ptr(), _stream(stream))
     return g
@@ -486,7 +511,7 @@ def hg_aca_fwd(src, dst, stream=None):
     B = _quad_rows(src, "src")
     if _quad_rows(dst, "dst") != B:
         raise ValueError("src and dst must have the same batch size")
-    H = torch.empty((B, 9), dtype=torch.float64, device=src.device)
+    (H,) = _new(stream, src.device, ((B, 9), torch.float64))
     _abi.call("hg_aca_fwd", src.data_ptr(), dst.data_ptr(), B, H.data_ptr(), _stream(stream))
     return H
 
@@ -499,8 +524,8 @@ def hg_aca_bwd(src, dst, grad_H, want_src=True, want_dst=True, stream=None):
     B = _quad_rows(src, "src")
     _quad_rows(dst, "dst")
     _c(grad_H, "grad_H", torch.float64)
-    gs = torch.empty_like(src) if want_src else None
-    gd = torch.empty_like(dst) if want_dst else None
+    gs = _new(stream, src.device, (src.shape, torch.float32))[0] if want_src else None
+    gd = _new(stream, dst.device, (dst.shape, torch.float32))[0] if want_dst else None
     _abi.call("hg_aca_bwd", src.data_ptr(), dst.data_ptr(), grad_H.data_ptr(), B,
               gs.data_ptr() if gs is not None else None,
               gd.data_ptr() if gd is not None else None, _stream(stream))
@@ -540,14 +565,12 @@ def _part_ws_bytes(B, h, w):
 def _part_ws(B, h, w, device, stream):
     """(pointer, bytes) of a workspace for a batch whose patches are cut into
     parts, and the tensor that holds it; (None, 0) and None when the batch is
-    not cut. The allocator hands the memory out again in stream order, so a
-    call on another stream than the current one is recorded."""
+    not cut. From the pool of the call's stream."""
     n = _part_ws_bytes(B, h, w)
     if not n:
         return (None, 0), None
-    ws = torch.empty(n, dtype=torch.uint8, device=device)
-    if stream is not None:
-        ws.record_stream(stream)
+    with _pool(stream, device):
+        ws = torch.empty(n, dtype=torch.uint8, device=device)
     return (ws.data_ptr(), n), ws
 
 
@@ -558,7 +581,7 @@ def hg_warp_l1_fwd(H, img, tgt, stream=None):
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
     _c(H, "H", torch.float64)
-    loss = torch.empty(B, dtype=torch.float32, device=img.device)
+    (loss,) = _new(stream, img.device, (B, torch.float32))
     ws, hold = _part_ws(B, h, w, img.device, stream)
     _abi.call("hg_warp_l1_fwd_ws", H.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h, w,
               loss.data_ptr(), *ws, _stream(stream))
@@ -573,7 +596,7 @@ def hg_warp_l1_bwd(H, img, tgt, grad_loss, stream=None):
     _img3(tgt, "tgt")
     _c(H, "H", torch.float64)
     _c(grad_loss, "grad_loss")
-    gH = torch.empty((B, 9), dtype=torch.float64, device=img.device)
+    (gH,) = _new(stream, img.device, ((B, 9), torch.float64))
     ws, hold = _part_ws(B, h, w, img.device, stream)
     _abi.call("hg_warp_l1_bwd_ws", H.data_ptr(), img.data_ptr(), tgt.data_ptr(),
               grad_loss.data_ptr(), B, h, w, gH.data_ptr(), *ws, _stream(stream))
@@ -582,7 +605,7 @@ def hg_warp_l1_bwd(H, img, tgt, grad_loss, stream=None):
 
 def hg_warp_store_fwd(H, img, stream=None):
     B, h, w = _img3(img, "img")
-    out = torch.empty_like(img)
+    (out,) = _new(stream, img.device, (img.shape, torch.float32))
     _abi.call("hg_warp_store_fwd", _c(H, "H", torch.float64).data_ptr(), img.data_ptr(), B, h, w,
               out.data_ptr(), _stream(stream))
     return out
@@ -591,7 +614,7 @@ def hg_warp_store_fwd(H, img, stream=None):
 def hg_l1_fwd(warped, tgt, stream=None):
     B, h, w = _img3(warped, "warped")
     _img3(tgt, "tgt")
-    loss = torch.empty(B, dtype=torch.float32, device=warped.device)
+    (loss,) = _new(stream, warped.device, (B, torch.float32))
     _abi.call("hg_l1_fwd", warped.data_ptr(), tgt.data_ptr(), B, h, w, loss.data_ptr(),
               _stream(stream))
     return loss
@@ -599,7 +622,7 @@ def hg_l1_fwd(warped, tgt, stream=None):
 
 def hg_l1_bwd(warped, tgt, grad_loss, stream=None):
     B, h, w = _img3(warped, "warped")
-    g = torch.empty_like(warped)
+    (g,) = _new(stream, warped.device, (warped.shape, torch.float32))
     _abi.call("hg_l1_bwd", warped.data_ptr(), _c(tgt, "tgt").data_ptr(),
               _c(grad_loss, "grad_loss").data_ptr(), B, h, w, g.data_ptr(), _stream(stream))
     return g
@@ -607,7 +630,7 @@ def hg_l1_bwd(warped, tgt, grad_loss, stream=None):
 
 def hg_warp_bwd_from_grad(H, img, grad_warped, stream=None):
     B, h, w = _img3(img, "img")
-    gH = torch.empty((B, 9), dtype=torch.float64, device=img.device)
+    (gH,) = _new(stream, img.device, ((B, 9), torch.float64))
     _abi.call("hg_warp_bwd_from_grad", _c(H, "H", torch.float64).data_ptr(), img.data_ptr(),
               _c(grad_warped, "grad_warped").data_ptr(), B, h, w, gH.data_ptr(), _stream(stream))
     return gH
@@ -657,7 +680,7 @@ def hg_photometric_fwd(offsets, img, tgt, stream=None):
     _c(offsets, "offsets")
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
-    loss = torch.empty(B, dtype=torch.float32, device=img.device)
+    (loss,) = _new(stream, img.device, (B, torch.float32))
     ws, hold = _part_ws(B, h, w, img.device, stream)
     _abi.call("hg_photometric_fwd_ws", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h, w,
               loss.data_ptr(), *ws, _stream(stream))
@@ -673,7 +696,7 @@ def hg_photometric_bwd(offsets, img, tgt, grad_loss, stream=None):
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
     _c(grad_loss, "grad_loss")
-    g = torch.empty((B, 4, 2), dtype=torch.float32, device=img.device)
+    (g,) = _new(stream, img.device, ((B, 4, 2), torch.float32))
     ws, hold = _part_ws(B, h, w, img.device, stream)
     _abi.call("hg_photometric_bwd_ws", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(),
               grad_loss.data_ptr(), B, h, w, g.data_ptr(), *ws, _stream(stream))
@@ -689,8 +712,7 @@ def hg_photometric_fwd_grad(offsets, img, tgt, stream=None):
     _c(offsets, "offsets")
     B, h, w = _img3(img, "img")
     _img3(tgt, "tgt")
-    loss = torch.empty(B, dtype=torch.float32, device=img.device)
-    g = torch.empty((B, 4, 2), dtype=torch.float32, device=img.device)
+    loss, g = _new(stream, img.device, (B, torch.float32), ((B, 4, 2), torch.float32))
     ws, hold = _part_ws(B, h, w, img.device, stream)
     _abi.call("hg_photometric_fwd_grad_ws", offsets.data_ptr(), img.data_ptr(), tgt.data_ptr(), B, h,
               w, loss.data_ptr(), g.data_ptr(), *ws, _stream(stream))
@@ -707,7 +729,7 @@ def hg_scale_grad(grad_unit, grad_loss, stream=None):
     B = grad_unit.shape[0]
     if tuple(grad_unit.shape) != (B, 4, 2) or grad_loss.numel() != B:
         raise ValueError("grad_unit must be (B, 4, 2) and grad_loss (B,)")
-    out = torch.empty_like(grad_unit)
+    (out,) = _new(stream, grad_unit.device, (grad_unit.shape, torch.float32))
     _abi.call("hg_scale_grad", grad_unit.data_ptr(), grad_loss.data_ptr(), B, out.data_ptr(),
               _stream(stream))
     return out
@@ -787,13 +809,23 @@ class Refine:
         self.loss = torch.empty(self.B, dtype=torch.float32, device=img.device) if with_loss else None
         n = _abi.lib().hg_refine_ws_bytes(self.B, self.h, self.w)
         self.ws = torch.empty(n, dtype=torch.uint8, device=img.device) if n else None
-        self._ws_stream = _stream() if n else None
+        made = torch.cuda.current_stream(img.device)
+        self._made_on = made.cuda_stream
+        self._made = None if torch.cuda.is_current_stream_capturing() else made.record_event()
 
-    def _record(self, raw, stream):
-        """Keeps the workspace from being handed out again before work queued on
-        another stream than the one it was allocated on has run."""
-        if self.ws is not None and raw != self._ws_stream:
-            self.ws.record_stream(torch.cuda.current_stream() if stream is None else stream)
+    def _ready(self, raw, stream):
+        """Before work on another stream than the one that loss and ws were made on:
+        behind what that stream had queued when they were made (it may still write
+        their memory), and not handed out again before the work has run."""
+        if raw == self._made_on:
+            return
+        with _pool(stream, self.img.device):
+            s = torch.cuda.current_stream(self.img.device)
+            if self._made is not None and not torch.cuda.is_current_stream_capturing():
+                s.wait_event(self._made)
+            for t in (self.loss, self.ws):
+                if t is not None:
+                    t.record_stream(s)
 
     def _args(self):
         ws = (None, 0) if self.ws is None else (self.ws.data_ptr(), self.ws.numel())
@@ -803,11 +835,13 @@ class Refine:
 
     def run(self, stream=None):
         raw = _stream(stream)
-        self._record(raw, stream)
+        self._ready(raw, stream)
         _abi.call("hg_refine_ws", *self._args(), raw)
         return self.offsets, self.loss
 
     def graph(self, stream=None):
         h = C.c_void_p()
-        _abi.call("hg_refine_graph_create_ws", *self._args(), _stream(stream), C.byref(h))
+        raw = _stream(stream)
+        self._ready(raw, stream)
+        _abi.call("hg_refine_graph_create_ws", *self._args(), raw, C.byref(h))
         return Graph(h, self)
