@@ -393,9 +393,14 @@ __device__ __forceinline__ void score_hyps(const RansacArgs &a, int64_t base, ui
 // becomes 0.5: t = 1 proves an inlier, t = 0 an outlier, and anything between
 // leaves the point open. Sums of t and t^2 per lane count the inliers and show
 // by their difference whether a point was open (0 and 1 are their own squares),
-// so counting needs neither compares nor ballots. Every kTileBlock tiles a lane
+// so counting needs neither compares nor ballots. Every TB tiles a lane
 // whose sums differ lists its points (one column of the block) for a float64
-// recount and leaves them out.
+// recount and leaves them out. Sums can also agree by rounding with a t just off
+// 0 or 1 among them: the difference, the sum of t (1 - t), is then within their
+// roundings, 2 TB halves of a last place of at most TB, so such t are within 2^-13
+// of 0 or 1, which the slack of the bound covers, and the sum of t within 2^-12 of
+// the whole number that it stands for, to which adding it to the total rounds it
+// (block_total).
 //
 // What bounds it: vector issue and the clock that the power limit leaves (1.95
 // GHz measured). Of gfx950's vector instructions only float add, mul, FMA (no
@@ -546,8 +551,8 @@ __device__ __forceinline__ uint32_t lane_here() {
 
 // Score the 32 hypotheses of operands au, av, aw (numbers m0 .. m0 + 31 in the
 // item) against tiles [t0, t1) of a segment of n points, whose first tile is
-// number first_tile of the pair; adds the inliers to tot (by result and lane)
-// and lists open points. Returns false if the item is abandoned (adaptive:
+// number first_tile of the pair; adds the inliers to tot (by result and lane;
+// block_total) and lists open points. Returns false if the item is abandoned (adaptive:
 // round hb is at or past the stopping hint, checked once per block of tiles).
 template <int TB, int CAP>
 __device__ __forceinline__ bool score_tiles(const RansacArgs &a, const float *X1, const float *Y1,
@@ -635,7 +640,7 @@ __device__ __forceinline__ bool score_tiles(const RansacArgs &a, const float *X1
       }
     }
 #pragma unroll
-    for (int i = 0; i < 16; ++i) tot[i][lane] += s[i];
+    for (int i = 0; i < 16; ++i) tot[i][lane] = block_total(tot[i][lane], s[i]);
   }
   return true;
 }
@@ -730,7 +735,7 @@ __device__ __forceinline__ uint32_t tile_count(const float (*tot)[64]) {
   uint32_t c = 0u;
 #pragma unroll
   for (int k = 0; k < 16; ++k)
-    c += static_cast<uint32_t>(tot[i][32 * h + 16 * (lane >> 5) + ((k + m) & 15)]);
+    c += total_count(tot[i][32 * h + 16 * (lane >> 5) + ((k + m) & 15)]);
   return c + __shfl_xor(c, 32);
 }
 
@@ -786,8 +791,8 @@ __device__ __forceinline__ uint32_t count_all(const RansacArgs &a, const float *
   return c;
 }
 
-// Points per segment of the tile loop: 32-bit point offsets, and per-lane float
-// totals below 2^24.
+// Points per segment of the tile loop: 32-bit point offsets, and per-lane totals
+// below 2^23.
 constexpr uint32_t kSegment = 1u << 28;
 
 // One item of the queue, placed: filled by one lane, read by the workgroup.
@@ -807,7 +812,7 @@ struct TileSmem {
   uint32_t valid[HB];
   uint32_t full[HB];       // 1: counted in float64 throughout
   uint32_t cnt[HB];
-  float tot[kWaves][16][64];   // per wave: inliers by result and lane
+  float tot[kWaves][16][64];   // per wave: inliers by result and lane, above kTotalZero
   OpenList<kGroupOpen> open;
   ItemSlot slot[2];
 };
@@ -879,7 +884,7 @@ __device__ __forceinline__ void group_score(const RansacArgs &a, int64_t base, u
     const uint32_t t0 = min(static_cast<uint32_t>(wave) * share, tiles), t1 = min(t0 + share, tiles);
     for (int ht = 0; ht < TileSmem<HB>::HT && t0 < t1; ++ht) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) sm.tot[wave][i][lane] = 0.0f;
+      for (int i = 0; i < 16; ++i) sm.tot[wave][i][lane] = kTotalZero;
       if (!score_tiles<TB>(a, X1 + seg, Y1 + seg, X2 + seg, Y2 + seg, ns, t0, t1, seg / 32u,
                            32u * ht, __builtin_bit_cast(bf16x8, sm.op[ht][0][lane]),
                            __builtin_bit_cast(bf16x8, sm.op[ht][1][lane]),

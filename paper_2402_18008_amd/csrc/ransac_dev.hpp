@@ -154,6 +154,18 @@ __device__ __forceinline__ bool inlier_f64(const double *H, float x1, float y1, 
   return W != 0.0 && fma(-tw, tw, fma(rv, rv, ru * ru)) <= 0.0;
 }
 
+// Running count of the tile form: a float at kTotalZero or above, where floats are
+// whole numbers, so that adding a block's sum of decisions rounds it to the whole
+// number it stands for (a truncation of the plain float total came out one short
+// where a sum was 3.9999998). For counts below 2^23.
+constexpr float kTotalZero = 8388608.0f;   // 2^23
+__host__ __device__ __forceinline__ float block_total(float total, float sum) {
+  return total + sum;
+}
+__host__ __device__ __forceinline__ uint32_t total_count(float total) {
+  return __builtin_bit_cast(uint32_t, total) - __builtin_bit_cast(uint32_t, kTotalZero);
+}
+
 // Packed argmax key: larger count wins, then the lower hypothesis index.
 // 0 means "no valid hypothesis".
 __device__ __forceinline__ unsigned long long pack_key(uint32_t count, uint32_t hyp) {
