@@ -473,7 +473,11 @@ __device__ __forceinline__ u32x4 row_operand(const float g[3], const float c[3],
 //   SW (27 u SW + 2.25 S) + 2 S^2,
 // which leaves a tenth for sigma's rounding and the float64 test's own error.
 // False: the magnitudes leave the range where that holds (the hypothesis is
-// then counted in float64 throughout).
+// then counted in float64 throughout). Of it: pieces below 2^-126 may read as zero
+// on the matrix cores, and a coordinate past 3.38e38 rounds to an infinite piece.
+// With coordinates below 1e18 and scaled entries below 1e25 (kMaxEntry) the former
+// move a row by less than 1e-12, and e, scaled, by less than 1e-6 of its bound.
+constexpr double kMaxEntry = 1.0e25;
 __device__ __forceinline__ bool tile_bound(const double *g, const Extent &x, float &bound) {
   constexpr float u = 5.9604645e-08f;   // 2^-24
   float s[3];
@@ -486,7 +490,7 @@ __device__ __forceinline__ bool tile_bound(const double *g, const Extent &x, flo
   const float mag = fmaf(x.r2[0] + x.r2[1], sw, s[0] + s[1]);
   const float S = (10.5f * u) * mag;
   bound = fmaf(sw, fmaf(27.0f * u, sw, 2.25f * S), fmaf(2.0f * S, S, 1.0e-35f));
-  return mag + sw < 1.0e18f && sw > 1.0e-18f;
+  return mag + sw < 1.0e18f && sw > 1.0e-18f && fmaxf(x.r1[0], x.r1[1]) < 1.0e18f;
 }
 
 // A hypothesis for the tile form: its float H, solver flags, and the rows g that
@@ -519,8 +523,13 @@ __device__ __forceinline__ uint32_t tile_hypothesis(const RansacArgs &a, int64_t
     full = !tile_bound(g, x, bound);
     // bound sigma^2 = 0.5 (to a rounding or two of the reciprocal root)
     const double sigma = static_cast<double>(__builtin_amdgcn_rsqf(2.0f * bound));
+    double top = 0.0;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) g[k] *= sigma;
+    for (int k = 0; k < 9; ++k) {
+      g[k] *= sigma;
+      top = fmax(top, fabs(g[k]));
+    }
+    full |= !(top < kMaxEntry);
   }
   if (f != 0u || full)
 #pragma unroll
