@@ -40,6 +40,7 @@
 
 #include "common.hpp"
 #include "ransac_dev.hpp"
+#include "tile_dev.hpp"
 
 namespace hg {
 
@@ -97,13 +98,6 @@ struct PairState {
 
 // Round key slot not yet published (no real key has all bits set).
 constexpr unsigned long long kUnpublished = ~0ull;
-
-// Where a pair's points lie (those with four finite coordinates; the others are
-// outliers to every hypothesis): x1 and y1 within r1 of c1, and x2 / tau and
-// y2 / tau, in the float arithmetic of the scoring, within r2 of k2.
-struct Extent {
-  float c1[2], k2[2], r1[2], r2[2];
-};
 
 // Hypotheses per round under adaptive termination (one work item).
 constexpr int kRoundHyps = 64;
@@ -414,85 +408,6 @@ __device__ __forceinline__ void score_hyps(const RansacArgs &a, int64_t base, ui
 // (l % 32) ^ 1, so that results i of u and i ^ 1 of v and w belong together:
 // the three results start at even registers, and equal indices would put all
 // sources of the squares into one bank (35.5 against 31.4 cycles).
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-// Two floats rounded to nearest bfloat16 (a in the low half).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 v = {static_cast<__bf16>(a), static_cast<__bf16>(b)};
-  return __builtin_bit_cast(uint32_t, v);
-}
-__device__ __forceinline__ float high_bf16(uint32_t p) {
-  return __uint_as_float(p & 0xffff0000u);
-}
-
-// Operand B of a point: this lane's coordinate c (x1 or y1); one = its
-// constants (1 1 or 1 0).
-__device__ __forceinline__ bf16x8 point_operand(float c, uint32_t one) {
-  u32x4 v;
-  v[0] = pack_bf16(c, c);
-  const float r1 = c - high_bf16(v[0]);
-  v[1] = pack_bf16(r1, r1);
-  const float r2 = r1 - high_bf16(v[1]);
-  v[2] = pack_bf16(c, r2);
-  v[3] = one;
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-// The three bfloat16 pieces of a float, as floats (their sum is exactly x).
-__device__ __forceinline__ void pieces(float x, float f[3]) {
-  f[0] = x;
-  f[1] = x - high_bf16(pack_bf16(0.0f, x));
-  f[2] = f[1] - high_bf16(pack_bf16(0.0f, f[1]));
-}
-
-// Operand A of one row, the slots of one half: g = its x1 or y1 coefficient, c =
-// its constant (rounded by pack_bf16, which leaves the pieces).
-__device__ __forceinline__ u32x4 row_operand(const float g[3], const float c[3], int half) {
-  u32x4 v;
-  v[0] = v[1] = pack_bf16(g[0], g[1]);
-  v[2] = pack_bf16(g[2], g[0]);
-  v[3] = half ? pack_bf16(c[2], 0.0f) : pack_bf16(c[0], c[1]);
-  return v;
-}
-
-// Bound on |e_computed - e| for the tile form over points with |x1 - c| <=
-// r1[0], |y1 - c| <= r1[1], |x2c| <= r2[0], |y2c| <= r2[1], rows g on centred
-// coordinates. With u = 2^-24, SU = |g0| r1[0] + |g1| r1[1] + |g2| and SV, SW
-// likewise, a row's product errs by at most 8.3 u of its magnitude sum (measured
-// over random, wide-range and cancelling operands: at most 5.4 u, 0.7 u rms; the
-// dropped products are at most 2 u of it), the rounding of g by 0.5 u, the centred
-// point and x2c by u each, so ru and rv together by S = 10.5 u (SU + SV +
-// (r2[0] + r2[1]) SW) beside their own rounding. A wrong decision needs the true
-// or the computed d = ru^2 + rv^2 at or below w^2 <= SW^2, hence |ru|, |rv| <=
-// SW (1 + small), and then the errors of the residuals (2 SW S + S^2), of w
-// (2 SW 8.6 u SW), of 1/tau (u SW^2) and of the squares, sums and the last FMA
-// (5 u SW^2) stay below
-//   SW (27 u SW + 2.25 S) + 2 S^2,
-// which leaves a tenth for sigma's rounding and the float64 test's own error.
-// False: the magnitudes leave the range where that holds (the hypothesis is
-// then counted in float64 throughout). Of it: pieces below 2^-126 may read as zero
-// on the matrix cores, and a coordinate past 3.38e38 rounds to an infinite piece.
-// With coordinates below 1e18 and scaled entries below 1e25 (kMaxEntry) the former
-// move a row by less than 1e-12, and e, scaled, by less than 1e-6 of its bound.
-constexpr double kMaxEntry = 1.0e25;
-__device__ __forceinline__ bool tile_bound(const double *g, const Extent &x, float &bound) {
-  constexpr float u = 5.9604645e-08f;   // 2^-24
-  float s[3];
-#pragma unroll
-  for (int r = 0; r < 3; ++r)
-    s[r] = fmaf(fabsf(static_cast<float>(g[3 * r])), x.r1[0],
-                fmaf(fabsf(static_cast<float>(g[3 * r + 1])), x.r1[1],
-                     fabsf(static_cast<float>(g[3 * r + 2]))));
-  const float sw = s[2];
-  const float mag = fmaf(x.r2[0] + x.r2[1], sw, s[0] + s[1]);
-  const float S = (10.5f * u) * mag;
-  bound = fmaf(sw, fmaf(27.0f * u, sw, 2.25f * S), fmaf(2.0f * S, S, 1.0e-35f));
-  return mag + sw < 1.0e18f && sw > 1.0e-18f && fmaxf(x.r1[0], x.r1[1]) < 1.0e18f;
-}
-
 // A hypothesis for the tile form: its float H, solver flags, and the rows g that
 // go into operand A (centred, scaled by 1/tau and sigma). full: without a bound, to be
 // counted in float64 throughout. An invalid, missing or full one gets u = 1024,
