@@ -345,6 +345,7 @@ PyObject *aca_bwd(PyObject *const *a) {
   NEED(a[5] == Py_None);
   const Tensor *s = quads(a[0]), *d = quads(a[1]), *g = packed(a[2], ScalarType::Double);
   NEED(s && d && g && s->size(0) == d->size(0) && g->numel() == 9 * s->size(0));
+  NEED(PyBool_Check(a[3]) && PyBool_Check(a[4]));
   const bool ws = a[3] == Py_True, wd = a[4] == Py_True;
   Tensor gs, gd;
   if (ws) gs = at::empty_like(s->detach());
