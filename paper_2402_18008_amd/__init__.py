@@ -108,10 +108,11 @@ def hg_solve_sk(obj, dst, H=None, flags=None, stream=None):
     planes). Returns (Hbar (9, n) planes, flags (n,), H_S1 (3, 3) float64
     numpy array) with the object-to-image homography Hbar H_S1 up to scale."""
     import numpy as np
-    r = _native and _native.solve_sk(tuple(map(float, obj)), dst, H, flags, stream)
+    obj = tuple(map(float, obj))   # once: it may be an iterator
+    r = _native and _native.solve_sk(obj, dst, H, flags, stream)
     if r is not None:
         return r[0], r[1], np.array(r[2], dtype=np.float64).reshape(3, 3)
-    o = (C.c_double * 8)(*[float(v) for v in obj])
+    o = (C.c_double * 8)(*obj)
     frame = (C.c_double * 9)()
     ld = _planes(dst, "dst", 8)
     n = dst.shape[1]

@@ -24,3 +24,32 @@ def test_truthy_flags(monkeypatch):
     for src in (s, s.clone().requires_grad_(True)):
         H = hg.ACAGeneral.apply(src, d.clone().requires_grad_(True))
         assert torch.isfinite(H).all()
+
+
+def test_pattern_from_an_iterator(monkeypatch):
+    """The pattern reaches the library whole when it can be read only once and the
+    native path leaves the call to the Python code."""
+    obj = [0.0, 0.0, 90.0, 0.0, 0.0, 80.0, 99.0, 95.0]
+    seen = []
+    monkeypatch.setattr(hg, "_dev", lambda t, name, dtype=torch.float32: t)
+    monkeypatch.setattr(hg, "_stream", lambda stream=None: 0)
+    monkeypatch.setattr(hg._abi, "call", lambda name, o, *a: seen.append(list(o)))
+    for form in (obj, iter(obj), (v for v in obj), np.array(obj)):
+        hg.hg_solve_sk(form, torch.zeros((8, 3)))
+    assert seen == [obj] * 4
+    with pytest.raises(IndexError):
+        hg.hg_solve_sk(obj + [1.0], torch.zeros((8, 3)))
+
+
+@pytest.mark.gpu
+def test_pattern_from_an_iterator_on_a_stream():
+    require_gpu()
+    obj = [0.0, 0.0, 90.0, 0.0, 0.0, 80.0, 99.0, 95.0]
+    g = torch.Generator(device="cuda").manual_seed(7)
+    dst = torch.rand((8, 50), generator=g, device="cuda") * 500
+    H, flags, frame = hg.hg_solve_sk(obj, dst)
+    torch.cuda.synchronize()
+    announce("pattern from an iterator, on a stream")
+    H2, flags2, frame2 = hg.hg_solve_sk(iter(obj), dst, stream=torch.cuda.Stream())
+    torch.cuda.synchronize()
+    assert torch.equal(H, H2) and torch.equal(flags, flags2) and np.array_equal(frame, frame2)
