@@ -84,14 +84,17 @@ PyObject *tuple(std::initializer_list<PyObject *> v) {
   return r;
 }
 
-// Runs a library call without the GIL; true if it succeeded.
+// Runs a library call without the GIL; true if it succeeded. The GIL is taken again
+// on every way out: reading a tensor's pointer may throw (one without storage).
+struct NoGil {
+  PyThreadState *state = PyEval_SaveThread();
+  ~NoGil() { PyEval_RestoreThread(state); }
+};
+
 template <class F>
 bool launch(F &&f) {
-  int st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
-  return st == HG_OK;
+  const NoGil released;
+  return f() == HG_OK;
 }
 
 #define DECLINE Py_RETURN_NONE

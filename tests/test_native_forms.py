@@ -53,3 +53,22 @@ def test_pattern_from_an_iterator_on_a_stream():
     H2, flags2, frame2 = hg.hg_solve_sk(iter(obj), dst, stream=torch.cuda.Stream())
     torch.cuda.synchronize()
     assert torch.equal(H, H2) and torch.equal(flags, flags2) and np.array_equal(frame, frame2)
+
+
+@pytest.mark.gpu
+def test_tensors_without_storage(monkeypatch):
+    """A sparse tensor where a buffer is expected has no pointer: an error, raised
+    with the interpreter's lock held."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(8)
+    s, d = (torch.rand((8, 50), generator=g, device="cuda") * 100 for _ in range(2))
+    flags = torch.zeros(50, dtype=torch.uint8, device="cuda").to_sparse()
+    ws = torch.ones(1 << 16, dtype=torch.uint8, device="cuda").to_sparse()
+    for name, fn in {
+        "solve4": lambda: hg.hg_solve4(s, d, flags=flags),
+        "affine": lambda: hg.hg_solve3_affine(s[:6], d[:6], flags=flags),
+        "sk": lambda: hg.hg_solve_sk([0.0, 0.0, 9.0, 0.0, 0.0, 8.0, 9.0, 9.0], d, flags=flags),
+        "ransac": lambda: hg.hg_ransac(s[:4], 64, 3.0, 1, ws=ws),
+        "sparse planes": lambda: hg.hg_solve4(s.to_sparse(), d),
+    }.items():
+        assert _same(name, fn, monkeypatch) == "error", name
