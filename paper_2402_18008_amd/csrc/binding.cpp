@@ -130,8 +130,9 @@ PyObject *solve4(PyObject *const *a) {
   NEED(a[5] == Py_None);
   int method;
   if (PyLong_CheckExact(a[2])) {
-    const long m = PyLong_AsLong(a[2]);
-    NEED(m == HG_ACA || m == HG_SKS);
+    int over;   // without an error where the number does not fit
+    const long m = PyLong_AsLongAndOverflow(a[2], &over);
+    NEED(!over && (m == HG_ACA || m == HG_SKS));
     method = static_cast<int>(m);
   } else {
     NEED(PyUnicode_CheckExact(a[2]));

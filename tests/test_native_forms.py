@@ -72,3 +72,14 @@ def test_tensors_without_storage(monkeypatch):
         "sparse planes": lambda: hg.hg_solve4(s.to_sparse(), d),
     }.items():
         assert _same(name, fn, monkeypatch) == "error", name
+
+
+@pytest.mark.parametrize("method", [2**70, -2**70, 2**63, -2**63, 2**31, -1, 2, True])
+def test_any_integer_as_method(monkeypatch, method):
+    """A number that is no method, or fits no machine integer, is left to the Python
+    code without an error of the native path's own."""
+    x = torch.zeros((8, 4))
+    if hg._native is None:
+        pytest.skip("_native.so not built")
+    assert hg._native.solve4(x, x, method, None, None, None) is None
+    assert _same("method", lambda: hg.hg_solve4(x, x, method), monkeypatch) == "error"
