@@ -217,7 +217,7 @@ def _ransac_out(n, n_hyp, want_counts, device, stream):
 
 
 def _ransac(name, corr, n_hyp, thresh, seed, want_counts, ws, stream):
-    r = _native and _native.ransac(name == "hg_ransac_plain", corr, int(n_hyp), float(thresh),
+    r = _native and _native.ransac(name == "hg_ransac_plain", corr, n_hyp, float(thresh),
                                    int(seed), want_counts, ws, stream)
     if r is not None:
         return r

@@ -83,3 +83,18 @@ def test_any_integer_as_method(monkeypatch, method):
         pytest.skip("_native.so not built")
     assert hg._native.solve4(x, x, method, None, None, None) is None
     assert _same("method", lambda: hg.hg_solve4(x, x, method), monkeypatch) == "error"
+
+
+@pytest.mark.gpu
+def test_number_of_hypotheses(monkeypatch):
+    """A fraction is no size of a counts tensor; without counts it is cut to an
+    integer, and integers of other types are taken."""
+    require_gpu()
+    corr = torch.rand((4, 50), generator=torch.Generator(device="cuda").manual_seed(9),
+                      device="cuda") * 500
+    for n, counts, kind in ((10.5, True, "error"), (10.0, True, "error"), ("10", True, "error"),
+                            (10.5, False, "value"), (np.int64(10), True, "value"),
+                            (10, True, "value")):
+        for fn in (hg.hg_ransac, hg.hg_ransac_plain):
+            assert _same(f"{n!r} hypotheses", lambda: fn(corr, n, 3.0, 1, counts),
+                         monkeypatch) == kind, n
