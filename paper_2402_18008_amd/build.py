@@ -51,15 +51,28 @@ def _run(cmd, what, verbose):
 
 def build_native(verbose=False):
     """_native.so: the host compiler, torch's headers and libraries; it finds
-    libhomog.so beside itself."""
+    libhomog.so beside itself. It is optional (without it every call goes through
+    ctypes), so where there is no compiler or a header is missing it is left out,
+    with a message, and one that was built before, against another libhomog, goes:
+    returns None then."""
     import torch
     root = os.path.dirname(torch.__file__)
+    python = sysconfig.get_paths()["include"]
+    cxx = shutil.which("g++") or shutil.which("c++")
+    needed = [os.path.join(root, "include", "torch", "csrc", "autograd", "python_variable.h"),
+              os.path.join(python, "Python.h")]
+    missing = [] if cxx else ["a C++ compiler"]
+    missing += [h for h in needed if not os.path.exists(h)]
+    if missing:
+        sys.stderr.write(f"_native.so is not built: {', '.join(missing)} not found\n")
+        if os.path.exists(NATIVE):
+            os.remove(NATIVE)
+        return None
     inc = [os.path.join(ROOT, "include"), os.path.join(root, "include"),
            os.path.join(root, "include", "torch", "csrc", "api", "include"),
-           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"),
-           sysconfig.get_paths()["include"]]
+           os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), python]
     tmp = NATIVE + ".tmp"
-    cmd = [shutil.which("g++") or "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
            "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            *(f for i in inc for f in ("-isystem", i)), "-o", tmp,
