@@ -247,7 +247,10 @@ int hg_ransac_adaptive(const float *corr, int64_t ld, const int64_t *off, int32_
  *   n_used         n_pairs int32 (output, may be NULL): points used.
  *   flags          n_pairs bytes (output, may be NULL): bit2 = fewer than 4
  *                  points or a singular normalised system; H written as 0.
- * One workgroup per pair (suited to sets of up to ~10^5 points).
+ * One workgroup per pair (suited to sets of up to ~10^5 points). Its size, and
+ * with it the order in which a pair's sums are added, follows from n_pairs and
+ * ld / n_pairs: the same points in a batch of another size, or in planes of
+ * another stride, may give an H that differs in its last bits.
  * Errors: n_pairs < 0, NULL corr/off/H with n_pairs > 0, ld < 1 ->
  * HG_EINVAL. n_pairs == 0 is a no-op.                                       */
 int hg_refit_ho(const float *corr, int64_t ld, const int64_t *off, int32_t n_pairs,
@@ -378,7 +381,10 @@ int hg_refine_graph_create(const float *img, const float *tgt, int32_t B, int32_
  * are cut into parts over several workgroups (double sums per part in ws, added
  * in a fixed order by a second, small launch; a refinement step adds them in
  * the next step's prologue). Results differ from the calls without a workspace
- * only by the order of those sums.
+ * only by the order of the sums: a thread's float terms, of which up to 16 are
+ * added before each conversion to double, are grouped differently, and the
+ * double sums are added in another order. Whether and how patches are cut
+ * follows from B, h and w, so a patch's last bits depend on the batch's size.
  *   ws: at least hg_photometric_ws_bytes(B, h, w) resp. hg_refine_ws_bytes
  *   bytes (0: a batch of this shape is not cut), 16-byte aligned, not shared
  *   with a call that may overlap; contents before and after do not matter.

@@ -2,7 +2,8 @@
 //
 // Two forms of scoring, both of which decide a point in float only where a bound
 // on the rounding error proves the decision and leave the rest to a float64
-// recount, so that every count is the float64 test's:
+// recount, so that every count is the float64 test's (error_bound in
+// ransac_dev.hpp, tile_bound in tile_dev.hpp, which also says what it rests on):
 //  * vector form (single pair): each lane holds P correspondences in registers,
 //    every lane reads the hypothesis from LDS, the inlier test runs per
 //    (hypothesis, point) and counts come from a wavefront ballot + popcount.
@@ -726,7 +727,8 @@ struct ItemSlot {
   uint32_t n, skip;
 };
 
-// Shared memory of a workgroup that takes an item together (kWaves waves).
+// Shared memory of a workgroup of the many-pair kernel, whose kWaves waves take an
+// item together.
 constexpr int kGroupOpen = 1024;
 template <int HB>
 struct TileSmem {
@@ -847,10 +849,8 @@ __device__ __forceinline__ void group_publish(const RansacArgs &a, int p, int hb
   }
 }
 
-// A persistent workgroup, taking items of HB hypotheses of one pair together:
-// for adaptive termination, where fewer rounds in flight mean fewer past the
-// stopping points, and for launches of few items. In the fixed-count form an
-// item's serial steps run beside each other: while one of waves 1 - 3 solves its
+// A persistent workgroup of any many-pair launch: its waves take items of HB
+// hypotheses of one pair together. In the fixed-count form an item's serial steps run beside each other: while one of waves 1 - 3 solves its
 // hypotheses, another takes the next item from the queue and wave 0 publishes
 // the item before. Adaptive rounds are published at once, and the next is taken
 // only then (taken ahead, 512 pairs of up to 8000 points: 382 us, not 337, by
@@ -1504,7 +1504,9 @@ static void write_tune_file() {
 // fewer than three to each resident workgroup and the pairs are large enough for
 // that to matter (64 pairs of up to 8000 points x 1024 hypotheses: 121 us with
 // 32, 135 us with 64; 512 pairs: 574 and 563 us; 64 pairs of up to 1000 points:
-// 61 and 60 us; 512 of up to 1000: 232 and 185 us).
+// 61 and 60 us; 512 of up to 1000: 232 and 185 us). The offsets are on the device, so
+// the plane stride stands for the number of points: a slice of longer planes gets
+// the shape of larger pairs (its speed alone depends on that).
 static hg_ransac_tuning lookup_tune(int n_pairs, int n_hyp, int64_t points) {
   std::lock_guard<std::mutex> lock(g_tune_mu);
   read_tune_file();
@@ -1619,7 +1621,8 @@ static int launch_batched(const RansacArgs &a0, const hg_ransac_tuning &t, void 
   // one wave per pair when ranking (ranks of 65536 pairs: 16384 workgroups)
   const int64_t prep_blocks = rank ? (static_cast<int64_t>(a.n_pairs) + kWaves - 1) / kWaves
                                    : (static_cast<int64_t>(a.n_pairs) + kThreads - 1) / kThreads;
-  // the extents: a workgroup per pair, or a wave where the pairs are small
+  // the extents: a workgroup per pair, or a wave where the pairs are small (by the
+  // plane stride, as in lookup_tune)
   const int pair_waves = a.ld / a.n_pairs >= 512 ? kWaves : 1;
   const int64_t ext_blocks = pair_waves == 1 ? (static_cast<int64_t>(a.n_pairs) + kWaves - 1) / kWaves
                                              : a.n_pairs;

@@ -477,7 +477,10 @@ __global__ __launch_bounds__(NT, WAVES) void refit_kernel(
 // threads, 19.3 with 512; of 1050, 12.0 and 12.1; of 550, 10.0 and 10.8). More
 // pairs than three 256-thread workgroups per compute unit are held to 128
 // registers, so that four fit (1024 pairs of 1050 points: 18.2 and 15.5 us; 4096 of
-// 300: 39.9 and 36.8); fewer lose by it (256 pairs: 8.5 and 8.8 us).
+// 300: 39.9 and 36.8); fewer lose by it (256 pairs: 8.5 and 8.8 us). The offsets are
+// on the device, so ld stands for the number of points: a slice of longer planes
+// gets the shape of larger pairs. The threads set the order of a pair's sums, and
+// with it their last bits.
 struct RefitShape {
   decltype(&refit_kernel<256, 1>) kernel;
   int threads;
