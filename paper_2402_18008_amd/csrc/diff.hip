@@ -576,11 +576,9 @@ __device__ __forceinline__ int warp_block(const double *Hb, const float *__restr
         if (MODE == kGradStored) {
           gi = tv[u] * iqf[u];
         } else {
-          // gl iq sign(r), with sign(0) = 0 (and 0 for a nan residual); gl and iq (q2 < 0
-          // where H reverses the orientation) have signs of their own
+          // gl iq sign(r), with sign(0) = 0 (and 0 for a nan residual)
           const float gq = gl * iqf[u];
-          const float gs = __uint_as_float(__float_as_uint(gq) ^ (__float_as_uint(r) & 0x80000000u));
-          gi = fabsf(r) > 0.0f ? gs : 0.0f;
+          gi = fabsf(r) > 0.0f ? copysignf(gq, r) : 0.0f;
         }
         gi = in ? gi : 0.0f;
         const float a0 = gi * t.dvdx, a1 = gi * t.dvdy;
