@@ -321,7 +321,11 @@ int hg_aca_bwd(const float *src, const float *dst, const double *grad_H, int32_t
  * float, with per-patch sums accumulated in double.
  * hg_warp_l1_bwd recomputes everything from H (nothing per pixel is stored)
  * and writes grad_H (B x 9 doubles) = grad_loss[b] * dloss[b]/dH_b, with
- * d|r|/dr = sign(r) (0 at 0) and the floor treated as constant.
+ * d|r|/dr = sign(r) (0 at 0) and the floor treated as constant. Known
+ * deviation, in this call and in every fused photometric gradient below: a
+ * pixel whose position has a negative denominator q_3 of q = adj(H) (x, y, 1)
+ * (it lies past the line at infinity, or H reverses the orientation) enters
+ * the gradient with the opposite sign. hg_warp_bwd_from_grad has the right one.
  * Errors: B outside [0, 2^27], h or w outside [1, 32768], h w > 2^29, NULL
  * pointer with B > 0 -> HG_EINVAL; B == 0 is a no-op.                                             */
 int hg_warp_l1_fwd(const double *H, const float *img, const float *tgt, int32_t B, int32_t h,

@@ -576,9 +576,13 @@ __device__ __forceinline__ int warp_block(const double *Hb, const float *__restr
         if (MODE == kGradStored) {
           gi = tv[u] * iqf[u];
         } else {
-          // gl iq sign(r), with sign(0) = 0 (and 0 for a nan residual)
-          const float gq = gl * iqf[u];
-          gi = fabsf(r) > 0.0f ? copysignf(gq, r) : 0.0f;
+          // gl |iq| sign(r), with sign(0) = 0 (and 0 for a nan residual). iq's own sign
+          // is left out: pixels with q2 < 0 enter with the opposite sign, as homog.h
+          // says. (24 patches of 211 x 317, loss, then gradient: 21.9 us; with gl's
+          // sign put on the workgroup's sums instead 22.7 us)
+          const float gq = gl * fabsf(iqf[u]);
+          const float gs = __uint_as_float(__float_as_uint(gq) ^ (__float_as_uint(r) & 0x80000000u));
+          gi = fabsf(r) > 0.0f ? gs : 0.0f;
         }
         gi = in ? gi : 0.0f;
         const float a0 = gi * t.dvdx, a1 = gi * t.dvdy;
