@@ -811,22 +811,24 @@ class Refine:
         n = _abi.lib().hg_refine_ws_bytes(self.B, self.h, self.w)
         self.ws = torch.empty(n, dtype=torch.uint8, device=img.device) if n else None
         made = torch.cuda.current_stream(img.device)
-        self._made_on = made.cuda_stream
+        self._ordered = {made.cuda_stream}   # streams that _ready has seen
         self._made = None if torch.cuda.is_current_stream_capturing() else made.record_event()
 
     def _ready(self, raw, stream):
         """Before work on another stream than the one that loss and ws were made on:
         behind what that stream had queued when they were made (it may still write
         their memory), and not handed out again before the work has run."""
-        if raw == self._made_on:
+        if raw in self._ordered:
             return
         with _pool(stream, self.img.device):
             s = torch.cuda.current_stream(self.img.device)
-            if self._made is not None and not torch.cuda.is_current_stream_capturing():
-                s.wait_event(self._made)
             for t in (self.loss, self.ws):
                 if t is not None:
                     t.record_stream(s)
+            if not torch.cuda.is_current_stream_capturing():
+                if self._made is not None:
+                    s.wait_event(self._made)
+                self._ordered.add(raw)   # what it is given later comes behind the wait
 
     def _args(self):
         ws = (None, 0) if self.ws is None else (self.ws.data_ptr(), self.ws.numel())

@@ -1,9 +1,9 @@
 // Native call path of the torch binding: the ordinary calls (plain contiguous
-// GPU tensors, the current stream) from argument checks to launch without
+// GPU tensors) from argument checks to launch without
 // going through Python and ctypes. Every function takes exactly the arguments
 // of its Python namesake and answers None for whatever it does not handle
-// itself (other tensor types, subclasses, wrapped tensors, a stream argument, a
-// bad shape, a failing call): the Python function then takes the call from the
+// itself (other tensor types, subclasses, wrapped tensors, a bad shape, a failing
+// call): the Python function then takes the call from the
 // start, with its own checks and errors. Host code only.
 //
 // What it is for: a call through the Python checks and ctypes costs 8 - 20 us of
@@ -14,12 +14,14 @@
 
 #include <ATen/Functions.h>
 #include <ATen/TensorSubclassLikeUtils.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstring>
 #include <exception>
 #include <limits>
+#include <optional>
 
 #include "homog.h"
 
@@ -50,7 +52,52 @@ const Tensor *planes(PyObject *o, int64_t k, int64_t &ld) {
   return t;
 }
 
-void *raw_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+// The stream of a call: the current one (None), or that of an object with a
+// cuda_stream handle. While it lives, tensors are allocated from that stream's pool
+// (_pool in __init__.py has the reason).
+class CallStream {
+ public:
+  void *raw = nullptr;
+
+  bool take(PyObject *o, const Tensor &like) {
+    if (o == Py_None) {
+      raw = c10::hip::getCurrentHIPStream().stream();
+      return true;
+    }
+    PyObject *handle = PyObject_GetAttrString(o, "cuda_stream");
+    const bool ok = handle && PyLong_CheckExact(handle);
+    raw = ok ? PyLong_AsVoidPtr(handle) : nullptr;
+    Py_XDECREF(handle);
+    if (!ok || PyErr_Occurred()) {
+      PyErr_Clear();
+      return false;
+    }
+    const c10::DeviceIndex device = like.device().index();
+    const c10::hip::HIPStream here = c10::hip::getCurrentHIPStream(device);
+    if (raw != here.stream()) {
+      c10::hip::setCurrentHIPStream(
+          raw ? c10::hip::getStreamFromExternal(static_cast<hipStream_t>(raw), device)
+              : c10::hip::getDefaultHIPStream(device));
+      here_ = here;
+    }
+    return true;
+  }
+
+  // A new output, which the caller will use on the current stream.
+  Tensor lend(Tensor t) const {
+    if (here_) c10::hip::HIPCachingAllocator::recordStream(t.storage().data_ptr(), *here_);
+    return t;
+  }
+
+  CallStream() = default;
+  CallStream(const CallStream &) = delete;
+  ~CallStream() {
+    if (here_) c10::hip::setCurrentHIPStream(*here_);
+  }
+
+ private:
+  std::optional<c10::hip::HIPStream> here_;   // the current stream, where it is another
+};
 
 Tensor empty(at::IntArrayRef size, ScalarType st, const Tensor &like) {
   return at::empty(size, at::TensorOptions().dtype(st).device(like.device()));
@@ -103,9 +150,9 @@ bool launch(F &&f) {
 
 // H (9 or 6 planes at stride ld) and flags of the solvers.
 bool solver_out(PyObject *Ho, PyObject *fo, int64_t rows, int64_t ld, int64_t n, const Tensor &like,
-                Out &H, Out &flags) {
+                const CallStream &st, Out &H, Out &flags) {
   if (Ho == Py_None) {
-    H.t = empty({rows, ld}, ScalarType::Float, like);
+    H.t = st.lend(empty({rows, ld}, ScalarType::Float, like));
     if (ld != n) H.t = H.t.slice(1, 0, n);
   } else {
     int64_t l;
@@ -115,7 +162,7 @@ bool solver_out(PyObject *Ho, PyObject *fo, int64_t rows, int64_t ld, int64_t n,
     H.t = *t;
   }
   if (fo == Py_None) {
-    flags.t = empty({n}, ScalarType::Byte, like);
+    flags.t = st.lend(empty({n}, ScalarType::Byte, like));
   } else {
     const Tensor *t = plain(fo, ScalarType::Byte);
     if (!t) return false;
@@ -127,7 +174,6 @@ bool solver_out(PyObject *Ho, PyObject *fo, int64_t rows, int64_t ld, int64_t n,
 
 // solve4(src, dst, method, H, flags, stream) -> (H, flags)
 PyObject *solve4(PyObject *const *a) {
-  NEED(a[5] == Py_None);
   int method;
   if (PyLong_CheckExact(a[2])) {
     int over;   // without an error where the number does not fit
@@ -148,35 +194,34 @@ PyObject *solve4(PyObject *const *a) {
   NEED(s && d && ld == ld2);
   const int64_t n = s->size(1);
   Out H, flags;
-  NEED(solver_out(a[3], a[4], 9, ld, n, *s, H, flags));
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[5], *s) && solver_out(a[3], a[4], 9, ld, n, *s, st, H, flags));
   NEED(launch([&] {
     return hg_solve4(method, ptr<float>(*s), ptr<float>(*d), n, ld, ptr<float>(H.t),
-                     ptr<uint8_t>(flags.t), st);
+                     ptr<uint8_t>(flags.t), st.raw);
   }));
   return tuple({H.take(), flags.take()});
 }
 
 // solve3_affine(src, dst, A, flags, stream) -> (A, flags)
 PyObject *solve3_affine(PyObject *const *a) {
-  NEED(a[4] == Py_None);
   int64_t ld, ld2;
   const Tensor *s = planes(a[0], 6, ld), *d = planes(a[1], 6, ld2);
   NEED(s && d && ld == ld2);
   const int64_t n = s->size(1);
   Out A, flags;
-  NEED(solver_out(a[2], a[3], 6, ld, n, *s, A, flags));
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[4], *s) && solver_out(a[2], a[3], 6, ld, n, *s, st, A, flags));
   NEED(launch([&] {
     return hg_solve3_affine(ptr<float>(*s), ptr<float>(*d), n, ld, ptr<float>(A.t),
-                            ptr<uint8_t>(flags.t), st);
+                            ptr<uint8_t>(flags.t), st.raw);
   }));
   return tuple({A.take(), flags.take()});
 }
 
 // solve_sk(obj, dst, H, flags, stream) -> (H, flags, 9 numbers of H_S1)
 PyObject *solve_sk(PyObject *const *a) {
-  NEED(a[4] == Py_None && PyTuple_CheckExact(a[0]) && PyTuple_GET_SIZE(a[0]) == 8);
+  NEED(PyTuple_CheckExact(a[0]) && PyTuple_GET_SIZE(a[0]) == 8);
   double obj[8], frame[9];
   for (int k = 0; k < 8; ++k) {
     PyObject *v = PyTuple_GET_ITEM(a[0], k);
@@ -188,11 +233,11 @@ PyObject *solve_sk(PyObject *const *a) {
   NEED(d);
   const int64_t n = d->size(1);
   Out H, flags;
-  NEED(solver_out(a[2], a[3], 9, ld, n, *d, H, flags));
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[4], *d) && solver_out(a[2], a[3], 9, ld, n, *d, st, H, flags));
   NEED(launch([&] {
     return hg_solve_sk(obj, ptr<float>(*d), n, ld, ptr<float>(H.t), ptr<uint8_t>(flags.t), frame,
-                       st);
+                       st.raw);
   }));
   PyObject *f = PyTuple_New(9);
   if (!f) return nullptr;
@@ -202,8 +247,7 @@ PyObject *solve_sk(PyObject *const *a) {
 
 // ransac(plain, corr, n_hyp, thresh, seed, want_counts, ws, stream) -> dict
 PyObject *ransac(PyObject *const *a) {
-  NEED(a[7] == Py_None && PyLong_CheckExact(a[2]) && PyFloat_CheckExact(a[3]) &&
-       PyLong_CheckExact(a[4]));
+  NEED(PyLong_CheckExact(a[2]) && PyFloat_CheckExact(a[3]) && PyLong_CheckExact(a[4]));
   int64_t ld;
   const Tensor *c = planes(a[1], 4, ld);
   NEED(c);
@@ -220,6 +264,8 @@ PyObject *ransac(PyObject *const *a) {
   const int counts = PyObject_IsTrue(a[5]);
   if (counts < 0) return nullptr;
   const size_t bytes = hg_ransac_ws_bytes(static_cast<int32_t>(n), static_cast<int32_t>(nh));
+  CallStream st;
+  NEED(st.take(a[7], *c));
   Tensor ws;
   if (a[6] == Py_None) {
     ws = empty({static_cast<int64_t>(bytes)}, ScalarType::Byte, *c);
@@ -228,17 +274,18 @@ PyObject *ransac(PyObject *const *a) {
     NEED(w && w->numel() >= static_cast<int64_t>(bytes));
     ws = *w;
   }
-  const Tensor H = empty({9}, ScalarType::Float, *c), cnt = empty({1}, ScalarType::Int, *c),
-               hyp = empty({1}, ScalarType::Int, *c), mask = empty({n}, ScalarType::Byte, *c);
+  const Tensor H = st.lend(empty({9}, ScalarType::Float, *c)),
+               cnt = st.lend(empty({1}, ScalarType::Int, *c)),
+               hyp = st.lend(empty({1}, ScalarType::Int, *c)),
+               mask = st.lend(empty({n}, ScalarType::Byte, *c));
   Tensor hc;
-  if (counts) hc = empty({nh}, ScalarType::Int, *c);
-  void *st = raw_stream();
+  if (counts) hc = st.lend(empty({nh}, ScalarType::Int, *c));
   auto *fn = PyObject_IsTrue(a[0]) ? hg_ransac_plain : hg_ransac;
   NEED(launch([&] {
     return fn(ptr<float>(*c), static_cast<int32_t>(n), ld, static_cast<int32_t>(nh), thresh, seed,
               ptr<float>(H), ptr<int32_t>(cnt), ptr<int32_t>(hyp), ptr<uint8_t>(mask),
               counts ? ptr<int32_t>(hc) : nullptr, ws.data_ptr(),
-              static_cast<size_t>(ws.numel()), st);
+              static_cast<size_t>(ws.numel()), st.raw);
   }));
   PyObject *r = PyDict_New();
   if (!r) return nullptr;
@@ -282,13 +329,13 @@ bool offsets_fit(PyObject *o, int64_t m, int64_t total) {
   return ok;
 }
 
-bool refit_out(PyObject *o, ScalarType st, at::IntArrayRef size, int64_t numel, const Tensor &like,
-               Out &out) {
+bool refit_out(PyObject *o, ScalarType type, at::IntArrayRef size, int64_t numel,
+               const Tensor &like, const CallStream &st, Out &out) {
   if (o == Py_None) {
-    out.t = empty(size, st, like);
+    out.t = st.lend(empty(size, type, like));
     return true;
   }
-  const Tensor *t = packed(o, st);
+  const Tensor *t = packed(o, type);
   if (!t || t->numel() < numel || t->device() != like.device()) return false;
   out.given = o;
   out.t = *t;
@@ -297,7 +344,7 @@ bool refit_out(PyObject *o, ScalarType st, at::IntArrayRef size, int64_t numel, 
 
 // refit_ho(corr, off, mask, H, n_used, flags, stream, off_host) -> (H, n_used, flags)
 PyObject *refit_ho(PyObject *const *a) {
-  NEED(a[6] == Py_None && a[7] != Py_None);
+  NEED(a[7] != Py_None);
   int64_t ld;
   const Tensor *c = planes(a[0], 4, ld), *off = packed(a[1], ScalarType::Long);
   NEED(c && off && off->dim() == 1 && off->numel() >= 1);
@@ -309,14 +356,15 @@ PyObject *refit_ho(PyObject *const *a) {
     NEED(mask && mask->numel() >= total);
   }
   Out H, used, flags;
-  NEED(refit_out(a[3], ScalarType::Float, {pairs, 9}, 9 * pairs, *c, H));
-  NEED(refit_out(a[4], ScalarType::Int, {pairs}, pairs, *c, used));
-  NEED(refit_out(a[5], ScalarType::Byte, {pairs}, pairs, *c, flags));
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[6], *c));
+  NEED(refit_out(a[3], ScalarType::Float, {pairs, 9}, 9 * pairs, *c, st, H));
+  NEED(refit_out(a[4], ScalarType::Int, {pairs}, pairs, *c, st, used));
+  NEED(refit_out(a[5], ScalarType::Byte, {pairs}, pairs, *c, st, flags));
   NEED(launch([&] {
     return hg_refit_ho(ptr<float>(*c), ld, ptr<int64_t>(*off), static_cast<int32_t>(pairs),
                        mask ? ptr<uint8_t>(*mask) : nullptr, ptr<float>(H.t),
-                       ptr<int32_t>(used.t), ptr<uint8_t>(flags.t), st);
+                       ptr<int32_t>(used.t), ptr<uint8_t>(flags.t), st.raw);
   }));
   return tuple({H.take(), used.take(), flags.take()});
 }
@@ -332,33 +380,34 @@ const Tensor *quads(PyObject *o) {
 
 // aca_fwd(src, dst, stream) -> H
 PyObject *aca_fwd(PyObject *const *a) {
-  NEED(a[2] == Py_None);
   const Tensor *s = quads(a[0]), *d = quads(a[1]);
   NEED(s && d && s->size(0) == d->size(0));
   const int64_t B = s->size(0);
-  const Tensor H = empty({B, 9}, ScalarType::Double, *s);
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[2], *s));
+  const Tensor H = st.lend(empty({B, 9}, ScalarType::Double, *s));
   NEED(launch([&] {
-    return hg_aca_fwd(ptr<float>(*s), ptr<float>(*d), static_cast<int32_t>(B), ptr<double>(H), st);
+    return hg_aca_fwd(ptr<float>(*s), ptr<float>(*d), static_cast<int32_t>(B), ptr<double>(H),
+                      st.raw);
   }));
   return THPVariable_Wrap(H);
 }
 
 // aca_bwd(src, dst, grad_H, want_src, want_dst, stream) -> (grad_src, grad_dst)
 PyObject *aca_bwd(PyObject *const *a) {
-  NEED(a[5] == Py_None);
   const Tensor *s = quads(a[0]), *d = quads(a[1]), *g = packed(a[2], ScalarType::Double);
   NEED(s && d && g && s->size(0) == d->size(0) && g->numel() == 9 * s->size(0));
   NEED(PyBool_Check(a[3]) && PyBool_Check(a[4]));
   const bool ws = a[3] == Py_True, wd = a[4] == Py_True;
   Tensor gs, gd;
-  if (ws) gs = at::empty_like(s->detach());
-  if (wd) gd = at::empty_like(d->detach());
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[5], *s));
+  if (ws) gs = st.lend(at::empty_like(s->detach()));
+  if (wd) gd = st.lend(at::empty_like(d->detach()));
   NEED(launch([&] {
     return hg_aca_bwd(ptr<float>(*s), ptr<float>(*d), ptr<double>(*g),
                       static_cast<int32_t>(s->size(0)), ws ? ptr<float>(gs) : nullptr,
-                      wd ? ptr<float>(gd) : nullptr, st);
+                      wd ? ptr<float>(gd) : nullptr, st.raw);
   }));
   return tuple({ws ? THPVariable_Wrap(gs) : Py_NewRef(Py_None),
                 wd ? THPVariable_Wrap(gd) : Py_NewRef(Py_None)});
@@ -396,15 +445,15 @@ const Tensor *sized(PyObject *o, ScalarType st, int64_t numel) {
 // photometric_fwd(offsets, img, tgt, stream) -> loss
 PyObject *photometric_fwd(PyObject *const *a) {
   Images im;
-  NEED(a[3] == Py_None && im.take(a[1], a[2]));
+  CallStream st;
+  NEED(im.take(a[1], a[2]) && st.take(a[3], *im.img));
   const Tensor *o = sized(a[0], ScalarType::Float, 8ll * im.B);
   NEED(o);
-  const Tensor loss = empty({im.B}, ScalarType::Float, *im.img);
+  const Tensor loss = st.lend(empty({im.B}, ScalarType::Float, *im.img));
   im.workspace();
-  void *st = raw_stream();
   NEED(launch([&] {
     return hg_photometric_fwd_ws(ptr<float>(*o), ptr<float>(*im.img), ptr<float>(*im.tgt), im.B,
-                                 im.h, im.w, ptr<float>(loss), im.wp(), im.wb(), st);
+                                 im.h, im.w, ptr<float>(loss), im.wp(), im.wb(), st.raw);
   }));
   return THPVariable_Wrap(loss);
 }
@@ -412,17 +461,17 @@ PyObject *photometric_fwd(PyObject *const *a) {
 // photometric_bwd(offsets, img, tgt, grad_loss, stream) -> grad_offsets
 PyObject *photometric_bwd(PyObject *const *a) {
   Images im;
-  NEED(a[4] == Py_None && im.take(a[1], a[2]));
+  CallStream st;
+  NEED(im.take(a[1], a[2]) && st.take(a[4], *im.img));
   const Tensor *o = sized(a[0], ScalarType::Float, 8ll * im.B),
                *gl = sized(a[3], ScalarType::Float, im.B);
   NEED(o && gl);
-  const Tensor g = empty({im.B, 4, 2}, ScalarType::Float, *im.img);
+  const Tensor g = st.lend(empty({im.B, 4, 2}, ScalarType::Float, *im.img));
   im.workspace();
-  void *st = raw_stream();
   NEED(launch([&] {
     return hg_photometric_bwd_ws(ptr<float>(*o), ptr<float>(*im.img), ptr<float>(*im.tgt),
                                  ptr<float>(*gl), im.B, im.h, im.w, ptr<float>(g), im.wp(),
-                                 im.wb(), st);
+                                 im.wb(), st.raw);
   }));
   return THPVariable_Wrap(g);
 }
@@ -430,33 +479,33 @@ PyObject *photometric_bwd(PyObject *const *a) {
 // photometric_fwd_grad(offsets, img, tgt, stream) -> (loss, grad_unit)
 PyObject *photometric_fwd_grad(PyObject *const *a) {
   Images im;
-  NEED(a[3] == Py_None && im.take(a[1], a[2]));
+  CallStream st;
+  NEED(im.take(a[1], a[2]) && st.take(a[3], *im.img));
   const Tensor *o = sized(a[0], ScalarType::Float, 8ll * im.B);
   NEED(o);
-  const Tensor loss = empty({im.B}, ScalarType::Float, *im.img),
-               g = empty({im.B, 4, 2}, ScalarType::Float, *im.img);
+  const Tensor loss = st.lend(empty({im.B}, ScalarType::Float, *im.img)),
+               g = st.lend(empty({im.B, 4, 2}, ScalarType::Float, *im.img));
   im.workspace();
-  void *st = raw_stream();
   NEED(launch([&] {
     return hg_photometric_fwd_grad_ws(ptr<float>(*o), ptr<float>(*im.img), ptr<float>(*im.tgt),
                                       im.B, im.h, im.w, ptr<float>(loss), ptr<float>(g), im.wp(),
-                                      im.wb(), st);
+                                      im.wb(), st.raw);
   }));
   return tuple({THPVariable_Wrap(loss), THPVariable_Wrap(g)});
 }
 
 // scale_grad(grad_unit, grad_loss, stream) -> grad_offsets
 PyObject *scale_grad(PyObject *const *a) {
-  NEED(a[2] == Py_None);
   const Tensor *u = packed(a[0], ScalarType::Float);
   NEED(u && u->dim() == 3 && u->size(1) == 4 && u->size(2) == 2 && u->size(0) <= (1 << 27));
   const Tensor *gl = sized(a[1], ScalarType::Float, u->size(0));
   NEED(gl);
-  const Tensor g = at::empty_like(u->detach());
-  void *st = raw_stream();
+  CallStream st;
+  NEED(st.take(a[2], *u));
+  const Tensor g = st.lend(at::empty_like(u->detach()));
   NEED(launch([&] {
     return hg_scale_grad(ptr<float>(*u), ptr<float>(*gl), static_cast<int32_t>(u->size(0)),
-                         ptr<float>(g), st);
+                         ptr<float>(g), st.raw);
   }));
   return THPVariable_Wrap(g);
 }
@@ -464,15 +513,15 @@ PyObject *scale_grad(PyObject *const *a) {
 // warp_l1_fwd(H, img, tgt, stream) -> loss
 PyObject *warp_l1_fwd(PyObject *const *a) {
   Images im;
-  NEED(a[3] == Py_None && im.take(a[1], a[2]));
+  CallStream st;
+  NEED(im.take(a[1], a[2]) && st.take(a[3], *im.img));
   const Tensor *H = sized(a[0], ScalarType::Double, 9ll * im.B);
   NEED(H);
-  const Tensor loss = empty({im.B}, ScalarType::Float, *im.img);
+  const Tensor loss = st.lend(empty({im.B}, ScalarType::Float, *im.img));
   im.workspace();
-  void *st = raw_stream();
   NEED(launch([&] {
     return hg_warp_l1_fwd_ws(ptr<double>(*H), ptr<float>(*im.img), ptr<float>(*im.tgt), im.B, im.h,
-                             im.w, ptr<float>(loss), im.wp(), im.wb(), st);
+                             im.w, ptr<float>(loss), im.wp(), im.wb(), st.raw);
   }));
   return THPVariable_Wrap(loss);
 }
@@ -480,17 +529,17 @@ PyObject *warp_l1_fwd(PyObject *const *a) {
 // warp_l1_bwd(H, img, tgt, grad_loss, stream) -> grad_H
 PyObject *warp_l1_bwd(PyObject *const *a) {
   Images im;
-  NEED(a[4] == Py_None && im.take(a[1], a[2]));
+  CallStream st;
+  NEED(im.take(a[1], a[2]) && st.take(a[4], *im.img));
   const Tensor *H = sized(a[0], ScalarType::Double, 9ll * im.B),
                *gl = sized(a[3], ScalarType::Float, im.B);
   NEED(H && gl);
-  const Tensor g = empty({im.B, 9}, ScalarType::Double, *im.img);
+  const Tensor g = st.lend(empty({im.B, 9}, ScalarType::Double, *im.img));
   im.workspace();
-  void *st = raw_stream();
   NEED(launch([&] {
     return hg_warp_l1_bwd_ws(ptr<double>(*H), ptr<float>(*im.img), ptr<float>(*im.tgt),
                              ptr<float>(*gl), im.B, im.h, im.w, ptr<double>(g), im.wp(), im.wb(),
-                             st);
+                             st.raw);
   }));
   return THPVariable_Wrap(g);
 }
@@ -508,14 +557,14 @@ bool rect(PyObject *const *a, float v[4]) {
 PyObject *aca_rect_fwd(PyObject *const *a) {
   float v[4];
   const Tensor *o = packed(a[0], ScalarType::Float);
-  NEED(a[5] == Py_None && o && o->dim() >= 1 && rect(a + 1, v));
+  CallStream st;
+  NEED(o && o->dim() >= 1 && rect(a + 1, v) && st.take(a[5], *o));
   const int64_t B = o->size(0);
   NEED(B <= (1 << 27) && o->numel() == 8 * B);
-  const Tensor H = empty({B, 9}, ScalarType::Double, *o);
-  void *st = raw_stream();
+  const Tensor H = st.lend(empty({B, 9}, ScalarType::Double, *o));
   NEED(launch([&] {
     return hg_aca_rect_fwd(ptr<float>(*o), static_cast<int32_t>(B), v[0], v[1], v[2], v[3],
-                           ptr<double>(H), st);
+                           ptr<double>(H), st.raw);
   }));
   return THPVariable_Wrap(H);
 }
@@ -524,15 +573,15 @@ PyObject *aca_rect_fwd(PyObject *const *a) {
 PyObject *aca_rect_bwd(PyObject *const *a) {
   float v[4];
   const Tensor *o = packed(a[0], ScalarType::Float);
-  NEED(a[6] == Py_None && o && o->dim() >= 1 && rect(a + 2, v));
+  CallStream st;
+  NEED(o && o->dim() >= 1 && rect(a + 2, v) && st.take(a[6], *o));
   const int64_t B = o->size(0);
   const Tensor *g = sized(a[1], ScalarType::Double, 9 * B);
   NEED(g && B <= (1 << 27) && o->numel() == 8 * B);
-  const Tensor go = empty({B, 4, 2}, ScalarType::Float, *o);
-  void *st = raw_stream();
+  const Tensor go = st.lend(empty({B, 4, 2}, ScalarType::Float, *o));
   NEED(launch([&] {
     return hg_aca_rect_bwd(ptr<float>(*o), ptr<double>(*g), static_cast<int32_t>(B), v[0], v[1],
-                           v[2], v[3], ptr<float>(go), st);
+                           v[2], v[3], ptr<float>(go), st.raw);
   }));
   return THPVariable_Wrap(go);
 }

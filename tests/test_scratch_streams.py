@@ -109,7 +109,8 @@ def test_refinement_waits_for_the_stream_that_made_its_buffers(monkeypatch):
     R = hg.Refine(img, img, off)
     R.run()
     assert not host.waits
-    R.run(stream=_Handle(9))
+    for _ in range(3):
+        R.run(stream=_Handle(9))
     R.graph(stream=_Handle(7))
     graph = hg.Graph(0, R)
     graph.launch(_Handle(5))
@@ -204,3 +205,68 @@ def test_streams_known_by_their_handle_alone():
             graph.launch(_Handle(raw))
             torch.cuda.synchronize()
             assert torch.equal(out, ref) and torch.isfinite(r.loss).all()
+
+
+@pytest.mark.gpu
+def test_native_path_takes_streams(monkeypatch):
+    """Calls with a stream go through the native path, allocate from that stream's
+    pool, leave the current stream as it was, and give what the Python path gives."""
+    require_gpu()
+    g = torch.Generator(device="cuda").manual_seed(12)
+    B, h, w = 8, 96, 128
+    img, tgt = (torch.randn((B, h, w), generator=g, device="cuda") for _ in range(2))
+    off = torch.rand((B, 4, 2), generator=g, device="cuda") * 4
+    gl = torch.rand(B, generator=g, device="cuda")
+    q = torch.rand((8, 99), generator=g, device="cuda") * 500
+    r = (0.0, 0.0, float(w - 1), 1.25)
+    H = hg.hg_aca_rect_fwd(off, *r)
+    gH = torch.randn((B, 9), generator=g, device="cuda", dtype=torch.float64)
+    po = torch.tensor([0, 40, 99], device="cuda")
+    side, here = torch.cuda.Stream(), torch.cuda.current_stream()
+    torch.cuda.synchronize()
+    pattern = [0.0, 0.0, 90.0, 0.0, 0.0, 80.0, 99.0, 95.0]
+    calls = {
+        "solve4": lambda **k: hg.hg_solve4(q, q + 1, "sks", **k),
+        "solve4 kept": lambda **k: hg.hg_solve4(q, q + 1, H=torch.zeros((9, 99), device="cuda"), **k),
+        "sk": lambda **k: hg.hg_solve_sk(pattern, q, **k)[:2],
+        "affine": lambda **k: hg.hg_solve3_affine(q[:6], q[:6] + 1, **k),
+        "ransac": lambda **k: tuple(hg.hg_ransac(q[:4], 64, 3.0, 1, **k).values()),
+        "refit": lambda **k: hg.hg_refit_ho(q[:4], po, off_host=[0, 40, 99], **k),
+        "refit native": lambda **k: hg.hg_refit_ho(q[:4], po, off_host=po.cpu(), **k),
+        "aca": lambda **k: (hg.hg_aca_fwd(off, off + 1, **k),),
+        "aca bwd": lambda **k: hg.hg_aca_bwd(off, off + 1, gH, **k),
+        "fwd": lambda **k: (hg.hg_photometric_fwd(off, img, tgt, **k),),
+        "bwd": lambda **k: (hg.hg_photometric_bwd(off, img, tgt, gl, **k),),
+        "both": lambda **k: hg.hg_photometric_fwd_grad(off, img, tgt, **k),
+        "scale": lambda **k: (hg.hg_scale_grad(off, gl, **k),),
+        "warp": lambda **k: (hg.hg_warp_l1_fwd(H, img, tgt, **k),),
+        "warp bwd": lambda **k: (hg.hg_warp_l1_bwd(H, img, tgt, gl, **k),),
+        "rect": lambda **k: (hg.hg_aca_rect_fwd(off, *r, **k),),
+        "rect bwd": lambda **k: (hg.hg_aca_rect_bwd(off, gH, *r, **k),),
+    }
+    for name, fn in calls.items():
+        want = fn()
+        torch.cuda.synchronize()
+        for stream in (side, here, _Handle(side.cuda_stream), _Handle(0)):
+            for native in (hg._native, None):
+                monkeypatch.setattr(hg, "_native", native)
+                announce(f"{name} on a stream, native {native is not None}")
+                if native is not None and name != "refit":   # a list of offsets is not its own
+                    monkeypatch.setattr(hg._abi, "call", lambda n, *a: pytest.fail(n))
+                torch.cuda.synchronize()
+                got = fn(stream=stream)
+                monkeypatch.undo()
+                assert torch.cuda.current_stream() == here
+                torch.cuda.synchronize()
+                assert all(torch.equal(x, y) for x, y in zip(got, want)), name
+    # a block that the call used is handed out again to its own stream only
+    blocks = torch.cuda.memory_snapshot
+    n = 3 << 20
+    out = hg.hg_solve4(torch.rand((8, n), device="cuda"), torch.rand((8, n), device="cuda"),
+                       stream=side)[0]
+    torch.cuda.synchronize()
+    seg = [s for s in blocks() if s["address"] <= out.data_ptr() < s["address"] + s["total_size"]]
+    assert [s["stream"] for s in seg] == [side.cuda_stream]
+    assert hg._native.solve4(q, q, 0, None, None, object()) is None
+    with pytest.raises(AttributeError):
+        hg.hg_solve4(q, q, stream=object())
