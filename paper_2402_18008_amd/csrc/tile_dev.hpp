@@ -1,6 +1,7 @@
 // The tile form's rows on the matrix cores: operands of one
-// v_mfma_f32_32x32x16_bf16 from floats split into bfloat16 pieces, and the bound
-// on the error of the decisions made from its results.
+// v_mfma_f32_32x32x16_bf16 from floats split into bfloat16 pieces (Henry, Tang and
+// Heinecke, ARITH 2019), and the bound on the error of the decisions made from its
+// results.
 #pragma once
 
 #include <hip/hip_runtime.h>
